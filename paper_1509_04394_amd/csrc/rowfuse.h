@@ -9,7 +9,7 @@
 //     stage keeps the few rows it still needs in registers (rings of 2r+1
 //     rows; the 5x5 window sums keep sums of row pairs instead, and share
 //     the pair sums of neighbouring columns across lanes), so nothing is
-//     staged in LDS and no barrier is needed;
+//     staged in LDS and no barrier is needed between rows;
 //   * horizontal neighbours come from the adjacent lanes through DPP wave
 //     shifts; a lane at the strip's edge receives its own edge value, which is
 //     exactly the replicate border when the strip touches the frame edge (and a
@@ -167,7 +167,7 @@ struct RowCtx {
     int W, Hf, x0, lane, y0, y1, t;
     int row_bytes;            // bytes per input row
     int lane_in, lane_out;    // byte offset of this lane's first column in an input / output row
-    bool real;                // frame t is one of the item's own frames (feature points)
+    bool pts;                 // frame t's feature points are wanted
     bool store;               // its output is written now (not at a frame boundary exchange)
     uint32_t valid;           // bit k: column k of this lane is an output column of the strip
     int lo_in, hi_in, lo_g, hi_g, lo_s, hi_s, lo_b, hi_b;
@@ -175,6 +175,7 @@ struct RowCtx {
     // [lo, hi) of each stage mapped to iterations (row = y0 - 6 + j - lag)
     int jp, np_, ji, ni, jg, ng, js, ns, jq, nq, jb, nb, jn, nn;
     uint8_t* prev;            // LDS previous-frame mask bits of this wavefront (DIFF)
+    uint32_t tag;             // frame t's number in the item << 16 (feature points)
 };
 
 // NB consecutive bytes at byte offset voff + soff of buffer r into a RawRow:
@@ -239,7 +240,8 @@ __device__ __forceinline__ void load_raw(const RowCtx& c, int row, RawRow<RowSta
 }
 
 template <int K, bool RGB, bool DIFF, bool EL, bool ER, int U>
-__device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, int j)
+__device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, PointList<K>& list,
+                                         int& ev, int j)
 {
     constexpr int U3 = U % 3, U5 = U % 5;
     const int row_in = c.y0 - ROW_HX + j;
@@ -355,12 +357,8 @@ __device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, 
             bits |= (nms_keep(centre[k], wmax) != 0u ? 1u : 0u) << k;
         }
         const uint32_t pts = bits & c.valid;
-        if (p.count != nullptr && c.real && __ballot(pts != 0u) != 0ull) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                emit_points(p, (pts >> k & 1u) != 0u, (uint32_t)c.t, (uint32_t)rn, (uint32_t)(c.x0 + K * c.lane + k),
-                            centre[k]);
-        }
+        const unsigned long long pm = __ballot(pts != 0u);
+        if (c.pts && pm != 0ull) list_put<K>(list, ev, pm, pts, (uint32_t)rn, (uint32_t)c.lane | c.tag, centre);
         uint32_t outbits = bits;
         if constexpr (DIFF) {
             uint8_t* slot = c.prev + (rn - c.y0) * 64 + c.lane;
@@ -389,10 +387,11 @@ __device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, 
 }
 
 template <int K, bool RGB, bool DIFF, bool EL, bool ER, int... U>
-__device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, int jb, int n,
+__device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p,
+                                          PointList<K>& list, int& ev, int jb, int n,
                                           std::integer_sequence<int, U...>)
 {
-    ((jb + U < n ? row_step<K, RGB, DIFF, EL, ER, U>(st, c, p, jb + U) : void()), ...);
+    ((jb + U < n ? row_step<K, RGB, DIFF, EL, ER, U>(st, c, p, list, ev, jb + U) : void()), ...);
 }
 
 // One side of a frame boundary between two runs of frames of the same strip
@@ -481,8 +480,8 @@ __device__ __forceinline__ RowBoundary row_boundary(const RowParams& rp, int str
 
 // All frames of one work item.
 template <int K, bool RGB, bool DIFF, bool EL, bool ER>
-__device__ __forceinline__ void row_frames(RowCtx& c, const RowParams& rp, int strip, int band, int ts, int t0,
-                                           int t1)
+__device__ __forceinline__ void row_frames(RowCtx& c, const RowParams& rp, PointList<K>& list, int& held, int strip,
+                                           int band, int ts, int t0, int t1)
 {
     const SegParams& p = rp.sp;
     constexpr int C = RGB ? 3 : 1;
@@ -491,17 +490,23 @@ __device__ __forceinline__ void row_frames(RowCtx& c, const RowParams& rp, int s
     const bool xch = DIFF && rp.xcount != nullptr;
     for (int t = ts; t < t1; ++t) {
         c.t = t;
-        c.real = t >= t0;
-        c.store = c.real && !(xch && t == t0 && t0 > 0);
+        c.pts = t >= t0 && p.count != nullptr;
+        c.tag = (uint32_t)(t - t0) << 16;
         c.in_frame = (const uint8_t*)p.in + (size_t)t * plane * C;
         c.out_frame = (uint8_t*)p.out + (size_t)t * plane;
-        RowState<K, RGB> st;
-        // first two input rows
-        const int r0 = c.y0 - ROW_HX;
-        load_raw<K, RGB>(c, r0, st.raw[0]);
-        load_raw<K, RGB>(c, r0 + 1, st.raw[1]);
-        for (int jb = 0; jb < n; jb += ROW_UNROLL)
-            row_block<K, RGB, DIFF, EL, ER>(st, c, p, jb, n, std::make_integer_sequence<int, ROW_UNROLL>{});
+        if (t > t0) list_room<K>(list, held, t - t0);
+        march_points<K>(list, held, [&](int& ev, bool again) {
+            c.store = t >= t0 && !(xch && t == t0 && t0 > 0) && !again;
+            RowState<K, RGB> st;
+            // first two input rows
+            const int r0 = c.y0 - ROW_HX;
+            load_raw<K, RGB>(c, r0, st.raw[0]);
+            load_raw<K, RGB>(c, r0 + 1, st.raw[1]);
+#pragma unroll 1
+            for (int jb = 0; jb < n; jb += ROW_UNROLL)
+                row_block<K, RGB, DIFF, EL, ER>(st, c, p, list, ev, jb, n,
+                                                std::make_integer_sequence<int, ROW_UNROLL>{});
+        });
         if constexpr (DIFF) {
             if (xch && t == t0 && t0 > 0) {  // the boundary before the run: this side is its first frame
                 const RowBoundary x = row_boundary<K>(rp, strip, band, t0 / rp.tt);
@@ -521,9 +526,10 @@ struct RowItem {
     int nstrips, band_h, tt, strip_step;
 };
 
-// One work item of one wavefront (all of it wavefront-uniform).
+// One work item of one wavefront (all of it wavefront-uniform).  Returns the
+// entries left in its point list.
 template <int K, bool RGB, bool DIFF>
-__device__ __forceinline__ void row_item(const RowParams& rp, const RowItem& it, uint8_t* prev_lds)
+__device__ __forceinline__ int row_item(const RowParams& rp, const RowItem& it, uint8_t* prev_lds, PointList<K>& list)
 {
     const SegParams& p = rp.sp;
     RowCtx c;
@@ -581,15 +587,18 @@ __device__ __forceinline__ void row_item(const RowParams& rp, const RowItem& it,
     const int t0 = it.chunk * it.tt;
     const int t1 = min(t0 + it.tt, p.T);
     const int ts = (DIFF && t0 > 0 && rp.xcount == nullptr) ? t0 - 1 : t0;
+    list_begin<K>(list, p, c.x0, t0);
+    int held = 0;
     const bool el = it.strip == 0, er = it.strip == it.nstrips - 1;
     if (el && er)
-        row_frames<K, RGB, DIFF, true, true>(c, rp, it.strip, it.band, ts, t0, t1);
+        row_frames<K, RGB, DIFF, true, true>(c, rp, list, held, it.strip, it.band, ts, t0, t1);
     else if (el)
-        row_frames<K, RGB, DIFF, true, false>(c, rp, it.strip, it.band, ts, t0, t1);
+        row_frames<K, RGB, DIFF, true, false>(c, rp, list, held, it.strip, it.band, ts, t0, t1);
     else if (er)
-        row_frames<K, RGB, DIFF, false, true>(c, rp, it.strip, it.band, ts, t0, t1);
+        row_frames<K, RGB, DIFF, false, true>(c, rp, list, held, it.strip, it.band, ts, t0, t1);
     else
-        row_frames<K, RGB, DIFF, false, false>(c, rp, it.strip, it.band, ts, t0, t1);
+        row_frames<K, RGB, DIFF, false, false>(c, rp, list, held, it.strip, it.band, ts, t0, t1);
+    return held;
 }
 
 // Decompose a clip-local item index.  Strips vary fastest, then bands, then
@@ -617,11 +626,15 @@ template <int K, bool RGB, bool DIFF>
 __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse(RowParams rp)
 {
     extern __shared__ uint8_t row_lds[];
+    __shared__ PointLists<K, ROW_WAVES> lists;
+    lists_begin(lists);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront-uniform
     const int item = blockIdx.x * ROW_WAVES + wave;
-    if (item >= rp.total) return;  // whole wavefront leaves; no barrier is used
+    if (item >= rp.total) return;  // whole wavefront leaves; no barrier is used from here on
     const RowItem it = row_decompose(item, rp.nstrips, rp.nbands, rp.nchunks, rp.band_h, rp.tt, rp.strip_step);
-    row_item<K, RGB, DIFF>(rp, it, row_lds + wave * rp.band_h * 64);
+    const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * rp.band_h * 64, lists.wave[wave]);
+    if (rp.sp.count != nullptr)
+        lists_end(lists, wave, held, min(ROW_WAVES, rp.total - (int)blockIdx.x * ROW_WAVES));
 }
 
 // ---------------------------------------------------------------- batches
@@ -654,6 +667,7 @@ template <int K, bool RGB, bool DIFF>
 __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse_batch(BatchParams bp)
 {
     extern __shared__ uint8_t row_lds[];
+    __shared__ PointList<K> lists[ROW_WAVES];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     for (;;) {
@@ -681,8 +695,17 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse_batch(BatchParams bp
         const RowItem it = row_decompose(item - bc.item_begin, bc.nstrips, bc.nbands, bc.nchunks, BATCH_BAND_H,
                                          BATCH_TT, 64 * K - 2 * ROW_HX);
         rp.tt = BATCH_TT;  // no exchange buffers: each run recomputes the frame before it
-        row_item<K, RGB, DIFF>(rp, it, row_lds + wave * BATCH_BAND_H * 64);
+        const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * BATCH_BAND_H * 64, lists[wave]);
+        list_flush<K>(lists[wave], held);  // the wavefronts of a workgroup work on different clips
     }
+}
+
+// Tall bands: the mask rows and the point lists pass the 64 KB a workgroup has
+// by default (the CU has 160 KB).
+inline hipError_t allow_row_lds(const void* kernel, size_t mask_rows)
+{
+    if (mask_rows + sizeof(PointLists<3, ROW_WAVES>) <= 65536) return hipSuccess;
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mask_rows);
 }
 
 hipError_t launch_rowfuse_batch(const BatchParams& bp, int K, bool rgb, bool diff, int blocks, hipStream_t s);

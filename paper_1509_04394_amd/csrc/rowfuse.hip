@@ -29,10 +29,12 @@ static hipError_t go(const RowParams& rp, hipStream_t s)
         const int nb = row_boundaries(rp.nstrips, rp.nbands, rp.nchunks);
         if (nb > 0) {
             hipLaunchKernelGGL(k_zero_words, dim3((nb + 255) / 256), dim3(256), 0, s, rp.xcount, nb);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+            const hipError_t z = hipGetLastError();
+            if (z != hipSuccess) return z;
         }
     }
+    const hipError_t e = allow_row_lds((const void*)k_rowfuse<K, RGB, DIFF>, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_rowfuse<K, RGB, DIFF>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
     return hipGetLastError();
 }

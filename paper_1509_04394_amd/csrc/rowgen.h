@@ -79,10 +79,13 @@ struct GenCtx {
     void* out;
     int W, Hf, x0, lane, y0, y1, t;
     size_t plane, vol;  // pixels per frame, pixels per channel volume
-    bool real;
+    bool pts, store;    // frame t's feature points are wanted; its output is written
     uint32_t valid;
     int lane_in;        // element offset of this lane's first column in an input row
     uint8_t* prev;
+    uint32_t tag;       // frame t's number in the item << 16 (feature points)
+    PointList<2>* list;  // this wavefront's points (LDS; groups with the suppression stage)
+    int* ev;            // entries found
 };
 
 template <int K, int R, bool EDGE>
@@ -216,12 +219,9 @@ __device__ __forceinline__ void gen_from(GenState<CH, A, B, K>& st, const GenCtx
 #pragma unroll
                 for (int k = 0; k < K; ++k) bits |= ((uint32_t)v[0][k] != 0u ? 1u : 0u) << k;
                 const uint32_t pts = bits & c.valid;
-                if (p.count != nullptr && c.real && __ballot(pts != 0u) != 0ull) {
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        emit_points(p, (pts >> k & 1u) != 0u, (uint32_t)c.t, (uint32_t)r_in,
-                                    (uint32_t)(c.lane_in + k), v[1][k]);
-                }
+                const unsigned long long pm = __ballot(pts != 0u);
+                if (c.pts && pm != 0ull)
+                    list_put<K>(*c.list, *c.ev, pm, pts, (uint32_t)r_in, (uint32_t)c.lane | c.tag, v[1]);
             }
             uint32_t outbits = bits;
             if constexpr (I::DIFF) {
@@ -230,7 +230,7 @@ __device__ __forceinline__ void gen_from(GenState<CH, A, B, K>& st, const GenCtx
                 *slot = (uint8_t)bits;
                 outbits = bits ^ prev;
             }
-            if (c.real) gen_store<CH, A, B, K>(c, r_in, v, outbits);
+            if (c.store) gen_store<CH, A, B, K>(c, r_in, v, outbits);
         }
     }
 }
@@ -391,25 +391,36 @@ __device__ __forceinline__ void gen_block(GenState<CH, A, B, K>& st, const GenCt
 }
 
 template <int CH, int A, int B, int K, bool EDGE>
-__device__ __forceinline__ void gen_frames(GenCtx& c, const SegParams& p, int ts, int t0, int t1)
+__device__ __forceinline__ void gen_frames(GenCtx& c, const SegParams& p, int& held, int ts, int t0, int t1)
 {
     using I = GenInfo<CH, A, B>;
     const int n = c.y1 - c.y0 + 2 * I::H;
-    const int lo_in = max(0, c.y0 - I::H), hi_in = min(c.Hf, c.y1 + I::H);
     for (int t = ts; t < t1; ++t) {
         c.t = t;
-        c.real = t >= t0;
-        GenState<CH, A, B, K> st;
-        const int r0 = c.y0 - I::H;
-        gen_load<CH, A, B, K>(c, r0, st.raw[0]);
-        gen_load<CH, A, B, K>(c, r0 + 1, st.raw[1]);
-        for (int jb = 0; jb < n; jb += ROW_UNROLL)
-            gen_block<CH, A, B, K, EDGE>(st, c, p, jb, n, std::make_integer_sequence<int, ROW_UNROLL>{});
+        c.pts = t >= t0 && p.count != nullptr;
+        c.tag = (uint32_t)(t - t0) << 16;
+        auto march = [&](int& ev, bool again) {
+            c.ev = &ev;
+            c.store = t >= t0 && !again;
+            GenState<CH, A, B, K> st;
+            const int r0 = c.y0 - I::H;
+            gen_load<CH, A, B, K>(c, r0, st.raw[0]);
+            gen_load<CH, A, B, K>(c, r0 + 1, st.raw[1]);
+#pragma unroll 1
+            for (int jb = 0; jb < n; jb += ROW_UNROLL)
+                gen_block<CH, A, B, K, EDGE>(st, c, p, jb, n, std::make_integer_sequence<int, ROW_UNROLL>{});
+        };
+        if constexpr (I::HAS_NMS) {
+            if (t > t0) list_room<K>(*c.list, held, t - t0);
+            march_points<K>(*c.list, held, march);
+        } else {
+            march(held, false);
+        }
     }
 }
 
 template <int CH, int A, int B, int K>
-__device__ __forceinline__ void gen_item(const SegParams& p, const RowItem& it, uint8_t* prev_lds)
+__device__ __forceinline__ int gen_item(const SegParams& p, const RowItem& it, uint8_t* prev_lds, PointList<K>* list)
 {
     using I = GenInfo<CH, A, B>;
     GenCtx c;
@@ -438,21 +449,36 @@ __device__ __forceinline__ void gen_item(const SegParams& p, const RowItem& it, 
     const int t0 = it.chunk * it.tt;
     const int t1 = min(t0 + it.tt, p.T);
     const int ts = (I::DIFF && t0 > 0) ? t0 - 1 : t0;
+    c.list = list;
+    if constexpr (I::HAS_NMS) list_begin<K>(*list, p, x0, t0);
+    int held = 0;
     if (it.strip == 0 || it.strip == it.nstrips - 1)
-        gen_frames<CH, A, B, K, true>(c, p, ts, t0, t1);
+        gen_frames<CH, A, B, K, true>(c, p, held, ts, t0, t1);
     else
-        gen_frames<CH, A, B, K, false>(c, p, ts, t0, t1);
+        gen_frames<CH, A, B, K, false>(c, p, held, ts, t0, t1);
+    return held;
 }
 
 template <int CH, int A, int B, int K>
 __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowgen(RowParams rp)
 {
+    using I = GenInfo<CH, A, B>;
     extern __shared__ uint8_t gen_lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int item = blockIdx.x * ROW_WAVES + wave;
-    if (item >= rp.total) return;
     const RowItem it = row_decompose(item, rp.nstrips, rp.nbands, rp.nchunks, rp.band_h, rp.tt, rp.strip_step);
-    gen_item<CH, A, B, K>(rp.sp, it, gen_lds + wave * rp.band_h * 64);
+    uint8_t* prev = gen_lds + wave * rp.band_h * 64;
+    if constexpr (I::HAS_NMS) {
+        __shared__ PointLists<K, ROW_WAVES> lists;
+        lists_begin(lists);
+        if (item >= rp.total) return;
+        const int held = gen_item<CH, A, B, K>(rp.sp, it, prev, &lists.wave[wave]);
+        if (rp.sp.count != nullptr)
+            lists_end(lists, wave, held, min(ROW_WAVES, rp.total - (int)blockIdx.x * ROW_WAVES));
+    } else {
+        if (item >= rp.total) return;
+        (void)gen_item<CH, A, B, K>(rp.sp, it, prev, nullptr);
+    }
 }
 
 template <int CH, int A, int B, int K>
@@ -463,6 +489,8 @@ hipError_t launch_rowgen_t(const RowParams& rp, hipStream_t s)
     } else {
         const int blocks = (rp.total + ROW_WAVES - 1) / ROW_WAVES;
         const size_t lds = GenInfo<CH, A, B>::DIFF ? (size_t)ROW_WAVES * rp.band_h * 64 : 0;
+        const hipError_t e = allow_row_lds((const void*)k_rowgen<CH, A, B, K>, lds);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_rowgen<CH, A, B, K>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
         return hipGetLastError();
     }
