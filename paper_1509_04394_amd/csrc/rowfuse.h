@@ -21,8 +21,8 @@
 //     frame it also writes it into the ring slots of the rows above, and after
 //     the last row it copies it into the slots of the rows below, one slot per
 //     iteration, once the consumer no longer needs the slot's old row;
-//   * the suppression mask feeds the frame difference through a per-wavefront
-//     LDS row of previous-frame mask bits; a work item covers a run of frames.
+//   * the suppression mask feeds the frame difference through the previous
+//     frame's mask bits, packed in LDS; a work item covers a run of frames.
 //     The difference at the first frame of a run needs the mask of the frame
 //     before it, which the item of the previous run computes anyway: the two
 //     items meet at their shared frame boundary (see row_exchange) instead of
@@ -47,10 +47,10 @@ struct RowParams {
     int tt;          // frames per work item
     // frame-boundary exchange (frame difference; null: recompute the frame
     // before each run instead): per boundary between runs c-1 and c of one
-    // strip and band, two mask areas of band_h * K words (the earlier run's
-    // last frame, the later run's first frame) and one arrival counter,
+    // strip and band, two mask areas of 64 words a mask group (the earlier
+    // run's last frame, the later run's first frame) and one arrival counter,
     // zeroed before the launch
-    uint64_t* xmask;
+    uint32_t* xmask;
     uint32_t* xcount;
 };
 
@@ -159,6 +159,7 @@ struct RowState {
     float rt[3][K];    // thresholded response
     float m[3][K];     // 3-wide horizontal maximum of rt
     RawRow<NB> raw[3];  // input rows, two loaded ahead
+    uint32_t mask, prev;  // this mask group's suppression bits, and the previous frame's
 };
 
 struct RowCtx {
@@ -174,7 +175,8 @@ struct RowCtx {
     // iteration j computes a stage's row iff (unsigned)(j - j*) < n*: the rows
     // [lo, hi) of each stage mapped to iterations (row = y0 - 6 + j - lag)
     int jp, np_, ji, ni, jg, ng, js, ns, jq, nq, jb, nb, jn, nn;
-    uint8_t* prev;            // LDS previous-frame mask bits of this wavefront (DIFF)
+    uint8_t* prev;            // LDS mask words of this wavefront, at this lane (DIFF)
+    uint32_t diff;            // all ones; zero on the clip's first frame, whose difference is zero
     uint32_t tag;             // frame t's number in the item << 16 (feature points)
 };
 
@@ -238,6 +240,9 @@ __device__ __forceinline__ void load_raw(const RowCtx& c, int row, RawRow<RowSta
     const int rc = row < 0 ? 0 : (row >= c.Hf ? c.Hf - 1 : row);
     load_words<RowState<K, RGB>::NB>(r, c.lane_in, rc * c.row_bytes, raw);
 }
+
+// 255 where bit `i` of w is set, else 0.
+__device__ __forceinline__ uint8_t byte_mask(uint32_t w, int i) { return (uint8_t)((int32_t)(w << (31 - i)) >> 31); }
 
 template <int K, bool RGB, bool DIFF, bool EL, bool ER, int U>
 __device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, PointList<K>& list,
@@ -359,19 +364,27 @@ __device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, 
         const uint32_t pts = bits & c.valid;
         const unsigned long long pm = __ballot(pts != 0u);
         if (c.pts && pm != 0ull) list_put<K>(list, ev, pm, pts, (uint32_t)rn, (uint32_t)c.lane | c.tag, centre);
-        uint32_t outbits = bits;
+        uint32_t out = bits;  // the row's K bits from bit SH on
+        constexpr int P = DIFF ? (U + 3) % ROW_UNROLL % row_mask_rows(K) : 0, SH = K * P;
         if constexpr (DIFF) {
-            uint8_t* slot = c.prev + (rn - c.y0) * 64 + c.lane;
-            const uint32_t prev = c.t == 0 ? bits : (uint32_t)*slot;
-            *slot = (uint8_t)bits;
-            outbits = bits ^ prev;
+            // row U of the unrolled loop is row P of its mask group
+            static_assert(ROW_UNROLL % row_mask_rows(K) == 0 && 2 * ROW_HX == 12, "row places are constants");
+            const int at = (rn - c.y0 - P) * row_mask_pitch(K);
+            if (P == 0) {
+                st.mask = bits;
+                st.prev = *(uint32_t*)(c.prev + at);  // not used on the first frame marched
+            } else {
+                st.mask |= bits << SH;
+            }
+            if (P == row_mask_rows(K) - 1) *(uint32_t*)(c.prev + at) = st.mask;
+            out = (st.mask ^ st.prev) & c.diff;
         }
         if (c.store) {
             const __amdgpu_buffer_rsrc_t r = out_rsrc(c.out_frame, (uint32_t)(c.W * c.Hf));
             const int soff = rn * c.W;  // uniform row offset
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                __builtin_amdgcn_raw_buffer_store_b8((outbits >> k & 1u) ? (uint8_t)255 : (uint8_t)0, r,
+                __builtin_amdgcn_raw_buffer_store_b8(byte_mask(out, SH + k), r,
                                                      (c.valid >> k & 1u) ? c.lane_out + k : DROP, soff, 0);
         }
     }
@@ -395,12 +408,11 @@ __device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c,
 }
 
 // One side of a frame boundary between two runs of frames of the same strip
-// and band: the mask of the frame next to the boundary on this side (held in
-// the LDS row of previous-frame bits) is published as K ballot words per row;
-// the side that arrives second reads the other side's words and writes the
-// frame difference of the later run's first frame (out_frame): the exclusive
-// or of the two masks, the same bits the later item would have formed from a
-// recomputed frame.  Neither side waits for the other.
+// and band: the mask of the frame next to the boundary on this side (the words
+// in LDS) is published; the side that arrives second reads the other side's
+// words and writes the frame difference of the later run's first frame
+// (out_frame): the exclusive or of the two masks, the same bits the later item
+// would have formed from a recomputed frame.  Neither side waits for the other.
 //
 // Every access to the exchange words and the counter is a device-scope
 // atomic read-modify-write, which the device performs coherently across its
@@ -410,71 +422,83 @@ __device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c,
 // writes back or invalidates the XCD's whole L2, which cost the kernel a
 // quarter of its speed (the strips of neighbouring items share input rows
 // in L2).
+//
+// Words of 15 rows a lane, as the row loop packs them.  With a byte a lane and
+// row in LDS and a ballot word a column and row in the exchange, forming and
+// taking the words apart cost about 0.45 of a frame an item: 800x600x1000 RGB
+// at 86 rows x 2 frames 1075 us (now 1016), gray 959 us (now 822; 764 without
+// the frame difference), 192x432x600 gray at 30 x 2 171 us (now 156).
 template <int K>
-__device__ __forceinline__ void row_exchange(const RowCtx& c, uint64_t* mine, uint64_t* other, uint32_t* cnt,
+__device__ __forceinline__ void row_exchange(const RowCtx& c, uint32_t* mine, uint32_t* other, uint32_t* cnt,
                                              uint8_t* out_frame)
 {
-    constexpr int RPC = 64 / K;  // rows per chunk: one word per lane
-    const int nrow = c.y1 - c.y0;
-    uint64_t sink = 0;
-    for (int r0 = 0; r0 < nrow; r0 += RPC) {
-        const int nr = min(RPC, nrow - r0);
-        uint64_t w = 0;  // lane (r - r0) K + k: word k of row r
-        for (int r = 0; r < nr; ++r) {
-            const uint32_t b = c.prev[(r0 + r) * 64 + c.lane];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const uint64_t m = __ballot((b >> k & 1u) != 0u);
-                if (c.lane == r * K + k) w = m;
-            }
-        }
-        if (c.lane < nr * K)
-            sink |= __hip_atomic_exchange(mine + r0 * K + c.lane, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    constexpr int G = row_mask_rows(K), STEP = G * row_mask_pitch(K);
+    constexpr int AHEAD = 6;  // words in flight
+    const int nrow = c.y1 - c.y0, ng = (nrow + G - 1) / G;
+    // the lane's number as a value of its own: addresses formed from it here
+    // would otherwise be kept in registers all through the row loop
+    int lane = c.lane;
+    asm volatile("" : "+v"(lane));
+    uint32_t sink = 0;
+#pragma unroll 1
+    for (int g = 0; g < ng; ++g)
+        sink |= __hip_atomic_exchange(mine + g * 64 + lane, *(uint32_t*)(c.prev + g * STEP), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
     // the exchanges have returned (so they are performed) before the arrival
     // is counted: the empty asm needs their results, and orders the memory
     // operations around it
-    const uint32_t sl = (uint32_t)sink, sh = (uint32_t)(sink >> 32);
-    asm volatile("" ::"v"(sl), "v"(sh) : "memory");
+    asm volatile("" ::"v"(sink) : "memory");
     uint32_t old = 0;
-    if (c.lane == 0) old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    old = __builtin_amdgcn_readfirstlane(__shfl(old, 0));
+    if (lane == 0) old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __builtin_amdgcn_readfirstlane(old);
     if (old == 0u) return;
     const __amdgpu_buffer_rsrc_t rs = out_rsrc(out_frame, (uint32_t)(c.W * c.Hf));
-    for (int r0 = 0; r0 < nrow; r0 += RPC) {
-        const int nr = min(RPC, nrow - r0);
-        uint64_t w = 0;
-        if (c.lane < nr * K)
-            w = __hip_atomic_fetch_or(other + r0 * K + c.lane, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int r = 0; r < nr; ++r) {
-            const uint32_t b = c.prev[(r0 + r) * 64 + c.lane];
-            uint32_t o = 0;
+#pragma unroll 1
+    for (int g0 = 0; g0 < ng; g0 += AHEAD) {
+        uint32_t w[AHEAD];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const uint64_t m = __shfl(w, r * K + k);
-                o |= (uint32_t)(m >> c.lane & 1u) << k;
+        for (int i = 0; i < AHEAD; ++i)  // past the last group: its words again
+            w[i] = __hip_atomic_fetch_or(other + min(g0 + i, ng - 1) * 64 + lane, 0u, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const int g = g0 + i;
+            if (g >= ng) break;
+            uint32_t x = w[i] ^ *(uint32_t*)(c.prev + g * STEP);
+            const int nr = min(G, nrow - g * G);
+            int soff = (c.y0 + g * G) * c.W;
+#pragma unroll 1
+            for (int r = 0; r < nr; ++r, soff += c.W, x >>= K) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b8(byte_mask(x, k), rs,
+                                                         (c.valid >> k & 1u) ? c.lane_out + k : DROP, soff, 0);
             }
-            const uint32_t outbits = b ^ o;
-            const int soff = (c.y0 + r0 + r) * c.W;
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                __builtin_amdgcn_raw_buffer_store_b8((outbits >> k & 1u) ? (uint8_t)255 : (uint8_t)0, rs,
-                                                     (c.valid >> k & 1u) ? c.lane_out + k : DROP, soff, 0);
         }
     }
 }
 
+// k_rowfuse's parameters in its kernel arguments, as an address the compiler
+// does not see through.
+typedef const __attribute__((address_space(4))) RowParams RowParamsK;
+__device__ __forceinline__ RowParamsK* kernel_params()
+{
+    auto k = (RowParamsK*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+}
+
 // Exchange areas of the boundary before run `chunk` (chunk >= 1).
 struct RowBoundary {
-    uint64_t* last;   // the earlier run's last frame
-    uint64_t* first;  // the later run's first frame
+    uint32_t* last;   // the earlier run's last frame
+    uint32_t* first;  // the later run's first frame
     uint32_t* cnt;
 };
 template <int K>
-__device__ __forceinline__ RowBoundary row_boundary(const RowParams& rp, int strip, int band, int chunk)
+__device__ __forceinline__ RowBoundary row_boundary(const RowParamsK& rp, int strip, int band, int chunk)
 {
     const size_t b = ((size_t)(chunk - 1) * rp.nbands + band) * rp.nstrips + strip;
-    const size_t words = (size_t)rp.band_h * K;
+    const size_t words = (size_t)row_mask_groups(K, rp.band_h) * 64;
     return RowBoundary{rp.xmask + 2 * b * words, rp.xmask + (2 * b + 1) * words, rp.xcount + b};
 }
 
@@ -488,10 +512,12 @@ __device__ __forceinline__ void row_frames(RowCtx& c, const RowParams& rp, Point
     const size_t plane = (size_t)p.W * p.H;
     const int n = c.y1 - c.y0 + 2 * ROW_HX;
     const bool xch = DIFF && rp.xcount != nullptr;
+    const bool want = p.count != nullptr;
     for (int t = ts; t < t1; ++t) {
         c.t = t;
-        c.pts = t >= t0 && p.count != nullptr;
+        c.pts = t >= t0 && want;
         c.tag = (uint32_t)(t - t0) << 16;
+        c.diff = t == 0 ? 0u : ~0u;
         c.in_frame = (const uint8_t*)p.in + (size_t)t * plane * C;
         c.out_frame = (uint8_t*)p.out + (size_t)t * plane;
         if (t > t0) list_room<K>(list, held, t - t0);
@@ -506,15 +532,23 @@ __device__ __forceinline__ void row_frames(RowCtx& c, const RowParams& rp, Point
             for (int jb = 0; jb < n; jb += ROW_UNROLL)
                 row_block<K, RGB, DIFF, EL, ER>(st, c, p, list, ev, jb, n,
                                                 std::make_integer_sequence<int, ROW_UNROLL>{});
+            if constexpr (DIFF) {  // the last mask group, where the band ends inside one
+                const int part = (c.y1 - c.y0) % row_mask_rows(K);
+                if (part != 0) *(uint32_t*)(c.prev + (c.y1 - c.y0 - part) * row_mask_pitch(K)) = st.mask;
+            }
         });
         if constexpr (DIFF) {
+            // (the launch's parameters are read again: kept through the row loop
+            // they would spill other scalars into vector registers)
             if (xch && t == t0 && t0 > 0) {  // the boundary before the run: this side is its first frame
-                const RowBoundary x = row_boundary<K>(rp, strip, band, t0 / rp.tt);
+                const RowParamsK& k = *kernel_params();
+                const RowBoundary x = row_boundary<K>(k, strip, band, t / k.tt);
                 row_exchange<K>(c, x.first, x.last, x.cnt, c.out_frame);
             }
             if (xch && t == t1 - 1 && t1 < p.T) {  // the boundary after the run: this side is its last frame
-                const RowBoundary x = row_boundary<K>(rp, strip, band, t1 / rp.tt);
-                row_exchange<K>(c, x.last, x.first, x.cnt, (uint8_t*)p.out + (size_t)t1 * plane);
+                const RowParamsK& k = *kernel_params();
+                const RowBoundary x = row_boundary<K>(k, strip, band, (t + 1) / k.tt);
+                row_exchange<K>(c, x.last, x.first, x.cnt, c.out_frame + (size_t)c.W * c.Hf);
             }
         }
     }
@@ -582,7 +616,7 @@ __device__ __forceinline__ int row_item(const RowParams& rp, const RowItem& it, 
     c.nq = c.lo_b + 2 - lo_q;
     c.jn = c.y0 + base + 6;
     c.nn = c.y1 - c.y0;
-    c.prev = prev_lds;
+    c.prev = prev_lds + 4 * c.lane;
 
     const int t0 = it.chunk * it.tt;
     const int t1 = min(t0 + it.tt, p.T);
@@ -623,7 +657,7 @@ __device__ __forceinline__ RowItem row_decompose(int item, int nstrips, int nban
 }
 
 template <int K, bool RGB, bool DIFF>
-__global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse(RowParams rp)
+__global__ __launch_bounds__(ROW_WAVES * 64, K == 2 ? (RGB ? 5 : 6) : 4) void k_rowfuse(RowParams rp)
 {
     extern __shared__ uint8_t row_lds[];
     __shared__ PointLists<K, ROW_WAVES> lists;
@@ -632,7 +666,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse(RowParams rp)
     const int item = blockIdx.x * ROW_WAVES + wave;
     if (item >= rp.total) return;  // whole wavefront leaves; no barrier is used from here on
     const RowItem it = row_decompose(item, rp.nstrips, rp.nbands, rp.nchunks, rp.band_h, rp.tt, rp.strip_step);
-    const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * rp.band_h * 64, lists.wave[wave]);
+    const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * row_mask_bytes(K, rp.band_h), lists.wave[wave]);
     if (rp.sp.count != nullptr)
         lists_end(lists, wave, held, min(ROW_WAVES, rp.total - (int)blockIdx.x * ROW_WAVES));
 }
@@ -695,7 +729,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse_batch(BatchParams bp
         const RowItem it = row_decompose(item - bc.item_begin, bc.nstrips, bc.nbands, bc.nchunks, BATCH_BAND_H,
                                          BATCH_TT, 64 * K - 2 * ROW_HX);
         rp.tt = BATCH_TT;  // no exchange buffers: each run recomputes the frame before it
-        const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * BATCH_BAND_H * 64, lists[wave]);
+        const int held = row_item<K, RGB, DIFF>(rp, it, row_lds + wave * row_mask_bytes(K, BATCH_BAND_H), lists[wave]);
         list_flush<K>(lists[wave], held);  // the wavefronts of a workgroup work on different clips
     }
 }

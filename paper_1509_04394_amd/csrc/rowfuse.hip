@@ -24,7 +24,7 @@ template <int K, bool RGB, bool DIFF>
 static hipError_t go(const RowParams& rp, hipStream_t s)
 {
     const int blocks = (rp.total + ROW_WAVES - 1) / ROW_WAVES;
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * rp.band_h * 64 : 0;
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.band_h) : 0;
     if (DIFF && rp.xcount != nullptr) {
         const int nb = row_boundaries(rp.nstrips, rp.nbands, rp.nchunks);
         if (nb > 0) {
@@ -55,7 +55,7 @@ hipError_t launch_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipSt
 template <int K, bool RGB, bool DIFF>
 static hipError_t go_batch(const BatchParams& bp, int blocks, hipStream_t s)
 {
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * BATCH_BAND_H * 64 : 0;
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, BATCH_BAND_H) : 0;
     hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -74,7 +74,7 @@ template <int K, bool RGB, bool DIFF>
 static int occ()
 {
     int n = 0;
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * BATCH_BAND_H * 64 : 0;
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, BATCH_BAND_H) : 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_rowfuse_batch<K, RGB, DIFF>, ROW_WAVES * 64, lds) !=
         hipSuccess)
         return 0;

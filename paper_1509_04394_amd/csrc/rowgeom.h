@@ -45,11 +45,26 @@ inline int row_strips_best(int W, bool rgb)
     return 2;
 }
 
+// Suppression mask of a band on the frame-difference kernels: a lane packs its
+// K bits of ROW_MASK_ROWS consecutive rows into one word (the row loop is
+// unrolled by 15, so a row's place in its word is a constant), and the words of
+// ROW_MASK_ROWS rows are ROW_MASK_ROWS * row_mask_pitch bytes apart in LDS (a
+// multiple of the row number, without a division).
+constexpr int row_mask_rows(int K) { return K == 2 ? 15 : 5; }
+constexpr int row_mask_pitch(int K) { return K == 2 ? 20 : 52; }  // >= 256 / row_mask_rows, bytes a row
+constexpr int row_mask_groups(int K, int band_h) { return (band_h + row_mask_rows(K) - 1) / row_mask_rows(K); }
+constexpr int row_mask_bytes(int K, int band_h)
+{
+    return row_mask_groups(K, band_h) * row_mask_rows(K) * row_mask_pitch(K);
+}
+// The on-chip memory a plan states for a frame-difference row group: a byte a
+// lane and row, which the generic row kernel takes and the packed words of the
+// Harris kernel stay below from 5 rows on.
 inline int row_lds_bytes(int band_h) { return ROW_WAVES * band_h * 64; }
 
 // Frame boundaries between consecutive runs of one strip and band, and the
-// device bytes of their exchange (two areas of band_h * K mask words and one
-// counter each, 256-byte aligned), for a frame-difference row group.
+// device bytes of their exchange (two areas of a word a lane and mask group and
+// one counter each, 256-byte aligned), for a frame-difference row group.
 FZ_HD inline int row_boundaries(int nstrips, int nbands, int nchunks)
 {
     return nchunks > 1 ? nstrips * nbands * (nchunks - 1) : 0;
@@ -57,8 +72,7 @@ FZ_HD inline int row_boundaries(int nstrips, int nbands, int nchunks)
 inline size_t row_exchange_bytes(int nstrips, int nbands, int nchunks, int band_h, int K)
 {
     const size_t nb = (size_t)row_boundaries(nstrips, nbands, nchunks);
-    const size_t words = ((2 * nb * band_h * K * 8) + 255) & ~(size_t)255;
-    return nb == 0 ? 0 : words + ((nb * 4 + 255) & ~(size_t)255);
+    return nb == 0 ? 0 : 2 * nb * row_mask_groups(K, band_h) * 256 + ((nb * 4 + 255) & ~(size_t)255);
 }
 
 // A frame-difference group keeps one byte of previous-frame mask bits per lane

@@ -54,8 +54,15 @@ size_t workspace_bytes(const fz_plan& p)
     return slots_bytes(p) + align256(ck) + xb;
 }
 
+size_t workspace_bytes_no_exchange(const fz_plan& p)
+{
+    size_t ck = 0;
+    for (const Segment& g : p.segs) ck = std::max(ck, ckpt_bytes(p, g));
+    return slots_bytes(p) + align256(ck);
+}
+
 fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
+                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream, bool exchange)
 {
     (void)hipGetLastError();  // drop an error latched by earlier, unrelated runtime calls
     hipStream_t s = (hipStream_t)stream;
@@ -110,12 +117,12 @@ fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_
             } else {
                 rp.strip_step = 64 * g.row_k - 2 * ROW_HX;
                 const size_t xb = exchange_bytes(p, g);
-                if (xb > 0) {
+                if (xb > 0 && exchange) {
                     if (!xch || ws_bytes < workspace_bytes(p))
                         return fail(FZ_E_WORKSPACE, "the frame-difference row group needs the exchange workspace");
                     const size_t nb = (size_t)row_boundaries(g.nstrips, g.nbands, g.nchunks);
-                    rp.xmask = (uint64_t*)xch;
-                    rp.xcount = (uint32_t*)(xch + ((2 * nb * g.tile_h * g.row_k * 8 + 255) & ~(size_t)255));
+                    rp.xmask = (uint32_t*)xch;
+                    rp.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
                 }
                 e = launch_rowfuse(rp, g.row_k, g.cfirst == 0, g.clast == 8, s);
             }

@@ -59,7 +59,11 @@ fz_status fz_run_chain_static(const fz_plan* plan, const void* d_in, void* d_out
     if (!plan || !d_in || !d_out) return fail(FZ_E_INVALID, "fz_run_chain_static: null plan or buffer");
     if (point_capacity > 0 && !d_points)
         return fail(FZ_E_INVALID, "fz_run_chain_static: capacity without a point buffer");
-    const size_t need = workspace_bytes(*plan);
+    // a frame-difference row group whose exchange words alone pass the limit
+    // runs without them, each item recomputing the frame before its run
+    size_t need = workspace_bytes(*plan);
+    const bool exchange = need <= FZ_STATIC_WORKSPACE_BYTES;
+    if (!exchange) need = workspace_bytes_no_exchange(*plan);
     if (need > FZ_STATIC_WORKSPACE_BYTES)
         return fail(FZ_E_WORKSPACE, "fz_run_chain_static: the plan needs " + std::to_string(need) +
                                         " bytes of workspace, more than the static " +
@@ -70,7 +74,7 @@ fz_status fz_run_chain_static(const fz_plan* plan, const void* d_in, void* d_out
         if (st != FZ_OK) return st;
     }
     return run_plan(*plan, d_in, d_out, d_points, d_point_count, point_capacity, ws, need > 0 ? FZ_STATIC_WORKSPACE_BYTES : 0,
-                    stream);
+                    stream, exchange);
 }
 
 }  // extern "C"

@@ -96,3 +96,29 @@ def test_frame_numbers_past_a_list_entry(dev):
     ref = run(GRAY7, x, W, H, T, 1e6, cap, dev, partition=[], engine="tile")
     got = run(GRAY7, x, W, H, T, 1e6, cap, dev, partition=[], engine="row", band_h=8, frames_per_block=T)
     assert ref[1] > 0 and ref[1] == got[1] and np.array_equal(ref[2], got[2]) and torch.equal(ref[0], got[0])
+
+
+# bands around the 15 rows of a packed mask word (5 with three columns a lane),
+# runs that meet at every frame, the recomputing path beside the exchange
+@pytest.mark.parametrize("ops,W,band", [(fz.HARRIS_CHAIN, 130, b) for b in (8, 14, 15, 16, 29, 30, 31, 44)] +
+                         [(fz.RGB_HARRIS_CHAIN, 365, b) for b in (8, 9, 10, 11, 26)])
+@pytest.mark.parametrize("tt", [1, 3])
+def test_packed_masks_meet_at_run_boundaries(dev, ops, W, band, tt):
+    H, T = 45, 8
+    x = torch.from_numpy(noise(W, H, T, 3 if W == 365 else 1, band)).to(dev)
+    ref = run(ops, x, W, H, T, 1e7, W * H * T, dev, partition=[], engine="tile")
+    got = run(ops, x, W, H, T, 1e7, W * H * T, dev, partition=[], engine="row", band_h=band, frames_per_block=tt)
+    assert torch.equal(ref[0], got[0]) and ref[1] == got[1] and np.array_equal(ref[2], got[2])
+
+
+def test_static_run_recomputes_where_the_exchange_does_not_fit(dev):
+    # 7 strips x 75 bands x 255 boundaries of 512 bytes: 69 MB of exchange words
+    W, H, T = 800, 600, 256
+    plan = fz.Plan(fz.HARRIS_CHAIN, W, H, T, partition=[], engine="row", band_h=8, frames_per_block=1)
+    assert plan.workspace_bytes > fz.FZ_STATIC_WORKSPACE_BYTES
+    x = torch.from_numpy(noise(W, H, 8, 1, 3)).to(dev).repeat(T // 8, 1, 1).contiguous()
+    ref, rp, rc = plan.run(x, *plan.alloc(dev, point_capacity=1))
+    out, pts, cnt, _ = plan.alloc(dev, point_capacity=1)
+    plan.run_static(x, out, pts, cnt)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and int(cnt.item()) == int(rc.item())
