@@ -93,10 +93,12 @@ Segment price_group_learned(const fz_plan& p, int a, int b, const float* prm, in
 double partition_dp(const double* cost, int n, std::vector<int>& seg_last);
 
 // Device side (run.hip)
-// exchange = false: frame-difference row groups recompute the frame before each
-// run (workspace_bytes_no_exchange() is enough).
 fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream, bool exchange = true);
+                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream);
+// The same with frame-difference row groups that recompute the frame before each
+// run (workspace_bytes_no_exchange() is enough).
+fz_status run_plan_no_exchange(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
+                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream);
 size_t workspace_bytes(const fz_plan& p);
 size_t workspace_bytes_no_exchange(const fz_plan& p);
 

@@ -88,7 +88,7 @@ Segment price_group(const fz_plan& p, int a, int b, int req_w, int req_h, int re
         s.row_k = row_generic ? 2 : row_strips_best(p.W, rgb_in);
         s.nstrips = row_strips(p.W, s.row_k, row_generic ? s.halo : ROW_HX);
         const int slots = row_generic ? ROW_SLOTS_GENERIC : row_slots(s.row_k, rgb_in);
-        const RowShape rs = row_shape(p.H, p.T, s.nstrips, diff, req_h, req_tpb, slots);
+        const RowShape rs = row_shape(p.H, p.T, s.nstrips, diff, req_h, req_tpb, slots, row_generic);
         if (rs.band_h == 0) {
             s.refused = 1;
             return s;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 
 #include "fz_ops.h"
 
@@ -10,9 +11,9 @@ namespace fz {
 constexpr int ROW_HX = 6;     // horizontal and vertical halo of the chain: 2 + 1 + 2 + 1
 constexpr int ROW_WAVES = 4;  // independent wavefronts per workgroup
 // Wavefronts per SIMD of the Harris row kernel, as its registers allow (512
-// per lane, allocated in blocks of 8): two columns per lane take <= 85
-// registers with RGB input (5 waves) and <= 80 with gray input (6 waves),
-// three columns <= 128 (4 waves).
+// per lane, allocated in blocks of 8; the kernel's launch bounds ask for these):
+// two columns per lane take 86 registers with RGB input (5 waves) and 80 with
+// gray input (6 waves), three columns <= 123 (4 waves).
 inline int row_waves(int K, bool rgb) { return K == 3 ? 4 : (rgb ? 5 : 6); }
 // Wavefronts the 256 CUs (4 SIMDs each) hold at once; 4 per SIMD is assumed
 // for the generic row kernel.
@@ -80,18 +81,25 @@ inline size_t row_exchange_bytes(int nstrips, int nbands, int nchunks, int band_
 // workgroup of ROW_WAVES wavefronts.
 constexpr int ROW_DIFF_MAX_BAND = 256;
 
-// Rows per band and frames per work item.  A work item marches band_h + 2*HX
-// rows per frame over tt frames (a frame-difference group takes the frame
-// before them from the previous run's item, which costs about 0.45 of a
-// frame per item); `slots` wavefronts run at once, fewer when the frame
-// difference's LDS rows (one workgroup of ROW_WAVES wavefronts per SIMD slot)
-// do not fit 160 KB per CU that many times.  The cost of a pair is its total
-// work, items x (band_h + 2*HX) x (tt + exchange), times (1 + 1/r) for r =
-// items / (wavefronts at once): a launch of few rounds of long items loses
-// the tail of its last round, and on the 800x600x1000 RGB chain measured
-// times fall from ~1.27 ms at 0.95 rounds (55 rows x 16 frames) to ~1.11 ms
-// at 5-8 rounds (55-86 rows x 2 frames); and times slots / (wavefronts at
-// once) where LDS holds fewer wavefronts than the registers allow.
+// Rows per band and frames per work item, from a model of the launch's time.
+//
+// Harris row kernel: an item of b rows x t frames takes
+//   w = (b + 8.9) (t + 0.15) + 9.7
+// row times (12 halo rows of which the first run only the first stages; the
+// frame-boundary exchange, 0.15 of a frame where there is one; the item's
+// start and end), and a launch of r = items / (wavefronts at once) rounds
+//   w (r + 0.083 (ceil(r) - r) + 0.9):
+// the work itself, part of the last round's idle share, and the first round's
+// latency, with few wavefronts a SIMD to hide it.  The five constants fit a
+// measured sweep (bands 4-160 x runs 1-8, 28 clips of 150x70x500 to
+// 800x600x1000, RGB and gray, with and without the frame difference): the
+// shape it picks is 0.9% slower than the best of the sweep on average, 4.5% at
+// worst.  Its predecessor, (b + 12) (t + 0.45) (1 + 1/r) with bands from 16
+// rows on, lost 11.7% on average and 27% on the smallest clips (320x240x4 RGB:
+// 16 rows 30.0 us, 4 rows 21.9; 800x600x200 RGB: 30 x 2 269 us, 67 x 1 246).
+//
+// Generic row kernel (one frame an item, halo rows as dear as others): the
+// total work, items x (b + 12), times (1 + 1/r), bands from 16 rows on.
 // Explicit requests (> 0)
 // are kept as given, except that a frame run longer than the video is the
 // whole video and a band taller than the frame the whole frame; a request the
@@ -100,12 +108,12 @@ constexpr int ROW_DIFF_MAX_BAND = 256;
 struct RowShape {
     int band_h, tt;
 };
-inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots)
+inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic)
 {
     if (req_h > 0 && diff && std::min(req_h, H) > ROW_DIFF_MAX_BAND) return RowShape{0, 0};
     RowShape best{0, 0};
     double best_cost = -1.0;
-    const int tts[] = {1, 2, 4, 8, 16, 32, 64};
+    const int tts[] = {1, 2, 3, 4, 8, 16, 32, 64}, least = generic ? 16 : 4;
     for (int tt : tts) {
         int t = tt;
         if (req_tt > 0) {
@@ -117,13 +125,21 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
         for (int nb = 1; nb <= H; ++nb) {
             const int bh = req_h > 0 ? std::min(req_h, H) : (H + nb - 1) / nb;
             if (diff && bh > ROW_DIFF_MAX_BAND) continue;
-            if (bh < 16 && req_h <= 0 && nb > 1) break;
+            if (bh < least && req_h <= 0 && nb > 1) break;
             const long long items = (long long)nstrips * ((H + bh - 1) / bh) * ((T + t - 1) / t);
-            long long fit = slots;
-            if (diff) fit = std::min(fit, (long long)256 * ROW_WAVES * (163840 / row_lds_bytes(bh)));
-            const double r = (double)items / (double)fit;
-            const double cost = (double)items * (bh + 2 * ROW_HX) * (t + (diff && t < T ? 0.45 : 0.0)) *
-                                (1.0 + 1.0 / r) * ((double)slots / (double)fit);
+            const double xch = diff && t < T ? 1.0 : 0.0;
+            double cost;
+            if (generic) {
+                // the mask rows in LDS (a byte a lane and row) can hold fewer wavefronts than the registers
+                long long fit = slots;
+                if (diff) fit = std::min(fit, (long long)256 * ROW_WAVES * (163840 / row_lds_bytes(bh)));
+                const double r = (double)items / (double)fit;
+                cost = (double)items * (bh + 2 * ROW_HX) * (t + 0.45 * xch) * (1.0 + 1.0 / r) * ((double)slots / (double)fit);
+            } else {
+                const double r = (double)items / (double)slots;
+                const double w = (bh + 8.9) * (t + 0.15 * xch) + 9.7;
+                cost = w * (r + 0.083 * (std::ceil(r) - r) + 0.9);
+            }
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best = RowShape{bh, t};

@@ -61,7 +61,7 @@ size_t workspace_bytes_no_exchange(const fz_plan& p)
     return slots_bytes(p) + align256(ck);
 }
 
-fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
+static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
                    uint32_t cap, void* d_ws, size_t ws_bytes, void* stream, bool exchange)
 {
     (void)hipGetLastError();  // drop an error latched by earlier, unrelated runtime calls
@@ -137,6 +137,18 @@ fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_
         cur_in = sp.out;
     }
     return FZ_OK;
+}
+
+fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
+                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
+{
+    return run_groups(p, d_in, d_out, d_points, d_count, cap, d_ws, ws_bytes, stream, true);
+}
+
+fz_status run_plan_no_exchange(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
+                               uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
+{
+    return run_groups(p, d_in, d_out, d_points, d_count, cap, d_ws, ws_bytes, stream, false);
 }
 
 }  // namespace fz

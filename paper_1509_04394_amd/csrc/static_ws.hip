@@ -73,8 +73,8 @@ fz_status fz_run_chain_static(const fz_plan* plan, const void* d_in, void* d_out
         const fz_status st = scratch_address(&ws);
         if (st != FZ_OK) return st;
     }
-    return run_plan(*plan, d_in, d_out, d_points, d_point_count, point_capacity, ws, need > 0 ? FZ_STATIC_WORKSPACE_BYTES : 0,
-                    stream, exchange);
+    return (exchange ? run_plan : run_plan_no_exchange)(*plan, d_in, d_out, d_points, d_point_count, point_capacity, ws,
+                                                        need > 0 ? FZ_STATIC_WORKSPACE_BYTES : 0, stream);
 }
 
 }  // extern "C"
