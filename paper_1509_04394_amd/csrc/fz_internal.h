@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -29,6 +30,8 @@ struct Segment {
     double cost;
     int refused;            // a request this group's kernel cannot run (cost is +inf): 1 a band, 2 an IIR frame run
     int ckpt;               // generic groups: IIR states checkpointed per frame run (two launches, workspace)
+    // generated groups: the group's source and its kernel on each device, set by jit_prepare
+    mutable std::shared_ptr<struct JitKernel> jit;
 };
 
 struct Params {
