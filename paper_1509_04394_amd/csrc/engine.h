@@ -563,26 +563,29 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_group(SegParams p)
 }
 
 // Groups without a window stage: one pass over the pixels.  Point stages need
-// no coordinates, so a frame is a flat array of W*H pixels; each thread takes
-// 4 consecutive pixels with vector loads and stores when the frame size is a
-// multiple of 4 and the buffers are 16-byte aligned (every plane then starts
-// 16-byte aligned for floats and 4-byte aligned for bytes), else one pixel.
+// no coordinates, so a clip is a flat array of W*H*T pixels per channel; each
+// thread takes 4 consecutive pixels with vector loads and stores, the last
+// thread the remainder.  The vectors are declared at their element's
+// alignment: an odd frame size or an odd buffer puts them anywhere, which the
+// memory path takes.  Bound by memory: the five point stages of the Harris chain
+// at 641x479x75 took 261 us with one pixel a thread (where a frame was no
+// multiple of four pixels) and take 222.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32u __attribute__((aligned(1)));
 template <int CH, int A, int B, int V>
-__device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, int t, size_t i)
+__device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, size_t vol, size_t i)
 {
     constexpr OpInfo oa = op_info(chain_op(CH, A));
     constexpr OpInfo ob = op_info(chain_op(CH, B));
     constexpr bool TEMPORAL = chain_op(CH, B) == FZ_OP_FRAMEDIFF;
     constexpr int E = pw_end(CH, A, B);
-    const size_t vol = plane * p.T;
     float v[V][3];
-    auto load = [&](int tt, float (&dst)[V][3]) {
-        const size_t off = (size_t)tt * plane + i;
+    auto load = [&](size_t off, float (&dst)[V][3]) {
         if constexpr (oa.op == FZ_OP_RGB2GRAY) {
             const uint8_t* s = (const uint8_t*)p.in + 3 * off;
             if constexpr (V == 4) {
-                const uint3 w = *(const uint3*)s;
-                const uint32_t b[3] = {w.x, w.y, w.z};
+                const u32u* w = (const u32u*)s;
+                const uint32_t b[3] = {w[0], w[1], w[2]};
 #pragma unroll
                 for (int k = 0; k < 12; ++k) dst[k / 3][k % 3] = (float)((b[k / 4] >> (8 * (k % 4))) & 255u);
             } else {
@@ -591,7 +594,7 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, int 
         } else if constexpr (oa.in_dt == FZ_U8) {
             const uint8_t* s = (const uint8_t*)p.in + off;
             if constexpr (V == 4) {
-                const uint32_t w = *(const uint32_t*)s;
+                const uint32_t w = *(const u32u*)s;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) dst[k][0] = (float)((w >> (8 * k)) & 255u);
             } else {
@@ -602,11 +605,9 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, int 
             for (int c = 0; c < oa.in_ch; ++c) {
                 const float* s = (const float*)p.in + c * vol + off;
                 if constexpr (V == 4) {
-                    const float4 w = *(const float4*)s;
-                    dst[0][c] = w.x;
-                    dst[1][c] = w.y;
-                    dst[2][c] = w.z;
-                    dst[3][c] = w.w;
+                    const f32x4u w = *(const f32x4u*)s;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) dst[k][c] = w[k];
                 } else {
                     dst[0][c] = s[0];
                 }
@@ -615,32 +616,48 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, int 
 #pragma unroll
         for (int k = 0; k < V; ++k) point_run<CH, A, E>(dst[k], p);
     };
-    load(t, v);
+    load(i, v);
     if constexpr (TEMPORAL) {
+        // the frame before; the clip's first frame differs from itself
         float u[V][3];
-        load(t > 0 ? t - 1 : 0, u);
+        if (i >= plane) {
+            load(i - plane, u);
+        } else {
+            const size_t at = i + V > plane ? i + V - plane : 0;  // pixels of the second frame
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                u[k][0] = v[k][0];
+                if (k + (int)at >= V) {
+                    const size_t j = i + k - plane;
+                    u[k][0] = (float)((const uint8_t*)p.in)[j];
+                }
+            }
+        }
 #pragma unroll
         for (int k = 0; k < V; ++k) v[k][0] = (float)framediff((uint32_t)v[k][0], (uint32_t)u[k][0]);
     }
-    const size_t off = (size_t)t * plane + i;
     if constexpr (ob.out_dt == FZ_U8) {
-        uint8_t* d = (uint8_t*)p.out + off;
+        uint8_t* d = (uint8_t*)p.out + i;
         if constexpr (V == 4) {
             uint32_t w = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) w |= ((uint32_t)v[k][0] & 255u) << (8 * k);
-            *(uint32_t*)d = w;
+            *(u32u*)d = w;
         } else {
             d[0] = (uint8_t)(uint32_t)v[0][0];
         }
     } else {
 #pragma unroll
         for (int c = 0; c < ob.out_ch; ++c) {
-            float* d = (float*)p.out + c * vol + off;
-            if constexpr (V == 4)
-                *(float4*)d = make_float4(v[0][c], v[1][c], v[2][c], v[3][c]);
-            else
+            float* d = (float*)p.out + c * vol + i;
+            if constexpr (V == 4) {
+                f32x4u w;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[k] = v[k][c];
+                *(f32x4u*)d = w;
+            } else {
                 d[0] = v[0][c];
+            }
         }
     }
 }
@@ -648,18 +665,13 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, int 
 template <int CH, int A, int B>
 __global__ __launch_bounds__(BLOCK_THREADS) void k_stream(SegParams p)
 {
-    const size_t plane = (size_t)p.W * p.H;
-    const int t = blockIdx.y;
-    const size_t stride = (size_t)gridDim.x * BLOCK_THREADS;
-    const bool aligned = (((uintptr_t)p.in | (uintptr_t)p.out) & 15u) == 0;
-    if (plane % 4 == 0 && aligned) {
-        const size_t n4 = plane / 4;
-        for (size_t q = (size_t)blockIdx.x * BLOCK_THREADS + threadIdx.x; q < n4; q += stride)
-            stream_px<CH, A, B, 4>(p, plane, t, 4 * q);
-    } else {
-        for (size_t i = (size_t)blockIdx.x * BLOCK_THREADS + threadIdx.x; i < plane; i += stride)
-            stream_px<CH, A, B, 1>(p, plane, t, i);
-    }
+    static_assert(chain_op(CH, B) != FZ_OP_FRAMEDIFF || A == B, "a streamed frame difference reads its u8 input as it is");
+    const size_t plane = (size_t)p.W * p.H, vol = plane * p.T;
+    const size_t i = ((size_t)blockIdx.x * BLOCK_THREADS + threadIdx.x) * 4;
+    if (i + 4 <= vol)
+        stream_px<CH, A, B, 4>(p, plane, vol, i);
+    else
+        for (size_t j = i; j < vol; ++j) stream_px<CH, A, B, 1>(p, plane, vol, j);
 }
 
 // Launch group A..B of chain CH with tile index `tile`.
@@ -669,11 +681,9 @@ hipError_t launch_group(const SegParams& p, int tile, hipStream_t s)
     if constexpr (A > B || B >= chain_len(CH) || A < 0) {
         return hipErrorInvalidValue;
     } else if constexpr (!group_has_window(CH, A, B)) {
-        const int n = p.W * p.H;
-        const int per = n % 4 == 0 ? n / 4 : n;
-        int bx = (per + BLOCK_THREADS - 1) / BLOCK_THREADS;
-        if (bx > 65535) bx = 65535;
-        hipLaunchKernelGGL((k_stream<CH, A, B>), dim3(bx, p.T), dim3(BLOCK_THREADS), 0, s, p);
+        const size_t blocks = ((size_t)p.W * p.H * p.T + 4 * BLOCK_THREADS - 1) / (4 * BLOCK_THREADS);
+        if (blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((k_stream<CH, A, B>), dim3((unsigned)blocks), dim3(BLOCK_THREADS), 0, s, p);
         return hipGetLastError();
     } else {
         auto go = [&](auto kern, int tw, int th) {
