@@ -323,9 +323,8 @@ size_t fz_batch_workspace_bytes(const fz_plan* plan, const fz_clip* clips, int32
 /* Run the plan's chain and partition over n_clips clips of possibly different
  * sizes and lengths (host array of descriptors).  Every clip's output and point
  * set equal those of fz_run_chain on that clip alone.  When the plan is a single
- * group the row kernel implements, all clips go through one persistent launch
- * whose wavefronts take (clip, strip, band, frame run) work items from a queue;
- * otherwise the clips' groups are launched clip after clip.  The launches are
+ * group the row kernel implements, all clips' (strip, band, frame run) work
+ * items go through one launch (one per 32 clips); otherwise the clips' groups are launched clip after clip.  The launches are
  * captured once into a HIP graph, kept in the plan and replayed while the clip
  * descriptors and workspace pointer stay the same (they are compared on every
  * call; a change re-captures).  A plan must not run batches on two streams at

@@ -1,5 +1,4 @@
-// Batches of clips: one persistent row-kernel launch over every clip's work
-// items when the plan is a single group the row kernel implements, otherwise
+// Batches of clips: one row-kernel launch over every clip's work items when the plan is a single group the row kernel implements, otherwise
 // the clips' groups one clip after another; either way captured once into a
 // HIP graph and replayed while the clip set is unchanged.
 #include <hip/hip_runtime.h>
@@ -13,7 +12,7 @@
 
 namespace fz {
 
-static bool batch_persistent(const fz_plan& p, const fz_clip* clips, int n)
+static bool batch_one_launch(const fz_plan& p, const fz_clip* clips, int n)
 {
     if (p.segs.size() != 1) return false;
     const Segment& g = p.segs[0];
@@ -23,11 +22,76 @@ static bool batch_persistent(const fz_plan& p, const fz_clip* clips, int n)
     return true;
 }
 
-constexpr size_t QUEUE_STRIDE = 256;  // one queue counter per launch, 256 bytes apart
+// The launch of clips[0..m) (m <= FZ_BATCH_MAX) but for its buffers' addresses:
+// every clip split as a share of the launch, so that a small clip of a large
+// batch gets tall bands too.  Offsets into the launch's workspace: the arrival
+// counters, then each clip's mask areas.
+struct BatchLaunch {
+    BatchParams bp;
+    int blocks;
+    size_t counters_at[FZ_BATCH_MAX], masks_at[FZ_BATCH_MAX], bytes;
+};
+static void batch_launch(const fz_plan& p, const fz_clip* clips, int m, BatchLaunch& l)
+{
+    const Segment& g = p.segs[0];
+    const bool rgb = g.cfirst == 0, diff = g.clast == 8;
+    double px = 0.0;
+    for (int i = 0; i < m; ++i) px += (double)clips[i].width * clips[i].height * clips[i].frames;
+    BatchParams& bp = l.bp;
+    bp = BatchParams{};
+    bp.n_clips = m;
+    size_t counters = 0, masks = 0;
+    int wgs = 0;
+    for (int i = 0; i < m; ++i) {
+        const fz_clip& c = clips[i];
+        BatchClip& b = bp.clip[i];
+        b.in = c.d_in;
+        b.out = c.d_out;
+        b.points = c.d_points;
+        b.count = p.has_nms ? c.d_point_count : nullptr;
+        b.cap = c.d_points ? c.point_capacity : 0u;
+        b.W = c.width;
+        b.H = c.height;
+        b.T = c.frames;
+        const double share = (double)c.width * c.height * c.frames / px;
+        RowGeom& r = b.g;
+        r.nstrips = row_strips(c.width, 2);
+        r.strip_step = 128 - 2 * ROW_HX;
+        const RowShape s = row_shape(c.height, c.frames, r.nstrips, diff, 0, std::min(BATCH_TT, c.frames),
+                                     std::max(1, (int)(row_slots(2, rgb) * share)), false);
+        r.band_h = s.band_h;
+        r.tt = s.tt;
+        r.nbands = (c.height + r.band_h - 1) / r.band_h;
+        r.nchunks = (c.frames + r.tt - 1) / r.tt;
+        r.total = r.nstrips * r.nbands * r.nchunks;
+        b.wg_begin = wgs;
+        wgs += (r.total + ROW_WAVES - 1) / ROW_WAVES;
+        bp.max_band = std::max(bp.max_band, r.band_h);
+        const size_t nb = diff ? (size_t)row_boundaries(r.nstrips, r.nbands, r.nchunks) : 0;
+        l.counters_at[i] = counters;
+        l.masks_at[i] = nb > 0 ? masks : (size_t)-1;
+        counters += nb * 4;
+        masks += 2 * nb * row_mask_groups(2, r.band_h) * 256;
+    }
+    const size_t head = (counters + 255) & ~(size_t)255;
+    for (int i = 0; i < m; ++i)
+        if (l.masks_at[i] != (size_t)-1) l.masks_at[i] += head;
+    bp.n_counters = (int)(counters / 4);
+    l.blocks = wgs;
+    l.bytes = std::max<size_t>(256, head + masks);
+}
 
 size_t batch_workspace_bytes(const fz_plan& p, const fz_clip* clips, int n)
 {
-    if (batch_persistent(p, clips, n)) return QUEUE_STRIDE * ((n + FZ_BATCH_MAX - 1) / FZ_BATCH_MAX);
+    if (batch_one_launch(p, clips, n)) {
+        size_t need = 0;
+        BatchLaunch l;
+        for (int c0 = 0; c0 < n; c0 += FZ_BATCH_MAX) {
+            batch_launch(p, clips + c0, std::min(n - c0, FZ_BATCH_MAX), l);
+            need += l.bytes;
+        }
+        return need;
+    }
     size_t mx = 0;
     for (int i = 0; i < n; ++i) {
         std::unique_ptr<fz_plan> cp(plan_for_size(p, clips[i].width, clips[i].height, clips[i].frames));
@@ -75,45 +139,29 @@ static std::vector<uint64_t> batch_key(const fz_clip* clips, int n, void* ws, si
 }
 
 // Enqueue the batch on stream s (being captured).
-static fz_status enqueue_batch(const fz_plan& p, const fz_clip* clips, int n, void* ws, size_t ws_bytes, hipStream_t s,
-                               int cus)
+static fz_status enqueue_batch(const fz_plan& p, const fz_clip* clips, int n, void* ws, size_t ws_bytes, hipStream_t s)
 {
-    if (batch_persistent(p, clips, n)) {
+    if (batch_one_launch(p, clips, n)) {
         const Segment& g = p.segs[0];
-        const bool rgb = g.cfirst == 0, diff = g.clast == 8;
-        int bpc = rowfuse_batch_blocks_per_cu(2, rgb, diff);
-        if (bpc < 1) bpc = 1;
+        char* at = (char*)ws;
+        BatchLaunch l;
         for (int c0 = 0; c0 < n; c0 += FZ_BATCH_MAX) {
             const int m = std::min(n - c0, FZ_BATCH_MAX);
-            BatchParams bp{};
+            batch_launch(p, clips + c0, m, l);
+            BatchParams& bp = l.bp;
             bp.gw.w0 = p.prm.gw[0];
             bp.gw.w1 = p.prm.gw[1];
             bp.gw.w2 = p.prm.gw[2];
             bp.k = p.prm.k;
             bp.thr = p.prm.thr;
-            bp.n_clips = m;
-            bp.queue = (uint32_t*)((char*)ws + QUEUE_STRIDE * (c0 / FZ_BATCH_MAX));
-            int items = 0;
-            for (int i = 0; i < m; ++i) {
-                const fz_clip& c = clips[c0 + i];
-                BatchClip& b = bp.clip[i];
-                b.in = c.d_in;
-                b.out = c.d_out;
-                b.points = c.d_points;
-                b.count = p.has_nms ? c.d_point_count : nullptr;
-                b.cap = c.d_points ? c.point_capacity : 0u;
-                b.W = c.width;
-                b.H = c.height;
-                b.T = c.frames;
-                b.nstrips = row_strips(c.width, 2);
-                b.nbands = (c.height + BATCH_BAND_H - 1) / BATCH_BAND_H;
-                b.nchunks = (c.frames + BATCH_TT - 1) / BATCH_TT;
-                b.item_begin = items;
-                items += b.nstrips * b.nbands * b.nchunks;
-            }
-            bp.total = items;
-            const int blocks = std::max(1, std::min((items + ROW_WAVES - 1) / ROW_WAVES, cus * bpc));
-            hipError_t e = launch_rowfuse_batch(bp, 2, rgb, diff, blocks, s);
+            bp.counters = (uint32_t*)at;
+            for (int i = 0; i < m; ++i)
+                if (l.masks_at[i] != (size_t)-1) {
+                    bp.clip[i].g.xmask = (uint32_t*)(at + l.masks_at[i]);
+                    bp.clip[i].g.xcount = (uint32_t*)(at + l.counters_at[i]);
+                }
+            at += l.bytes;
+            const hipError_t e = launch_rowfuse_batch(bp, g.cfirst == 0, g.clast == 8, l.blocks, s);
             if (e != hipSuccess) return fail(FZ_E_HIP, std::string("batch launch: ") + hipGetErrorString(e));
         }
         return FZ_OK;
@@ -139,10 +187,7 @@ fz_status run_batch(fz_plan& p, const fz_clip* clips, int n, void* ws, size_t ws
         return FZ_OK;
     }
     release_graph(p);
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return fail(FZ_E_HIP, std::string("device query: ") + hipGetErrorString(e));
+    hipError_t e = hipSuccess;
     if (!p.capture_stream) {
         hipStream_t cs = nullptr;
         e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
@@ -163,7 +208,7 @@ fz_status run_batch(fz_plan& p, const fz_clip* clips, int n, void* ws, size_t ws
     }
     e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return fail(FZ_E_HIP, std::string("begin capture: ") + hipGetErrorString(e));
-    fz_status st = enqueue_batch(p, clips, n, ws, ws_bytes, cs, cus);
+    fz_status st = enqueue_batch(p, clips, n, ws, ws_bytes, cs);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(cs, &g);
     if (st != FZ_OK) {

@@ -3,12 +3,12 @@
 
 namespace fz {
 
-// Zero the queue counter and every clip's point count (a kernel, so that the
+// Zero the arrival counters and every clip's point count (a kernel, so that the
 // reset is an ordinary kernel node when the batch is captured into a graph).
 __global__ void k_batch_reset(BatchParams bp)
 {
-    const int i = threadIdx.x;
-    if (i == 0) *bp.queue = 0u;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < bp.n_counters) bp.counters[i] = 0u;
     if (i < bp.n_clips && bp.clip[i].count != nullptr) *bp.clip[i].count = 0u;
 }
 
@@ -23,12 +23,12 @@ __global__ void k_zero_words(uint32_t* p, int n)
 template <int K, bool RGB, bool DIFF>
 static hipError_t go(const RowParams& rp, hipStream_t s)
 {
-    const int blocks = (rp.total + ROW_WAVES - 1) / ROW_WAVES;
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.band_h) : 0;
-    if (DIFF && rp.xcount != nullptr) {
-        const int nb = row_boundaries(rp.nstrips, rp.nbands, rp.nchunks);
+    const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.g.band_h) : 0;
+    if (DIFF && rp.g.xcount != nullptr) {
+        const int nb = row_boundaries(rp.g.nstrips, rp.g.nbands, rp.g.nchunks);
         if (nb > 0) {
-            hipLaunchKernelGGL(k_zero_words, dim3((nb + 255) / 256), dim3(256), 0, s, rp.xcount, nb);
+            hipLaunchKernelGGL(k_zero_words, dim3((nb + 255) / 256), dim3(256), 0, s, rp.g.xcount, nb);
             const hipError_t z = hipGetLastError();
             if (z != hipSuccess) return z;
         }
@@ -52,40 +52,23 @@ hipError_t launch_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipSt
     return hipErrorInvalidValue;
 }
 
-template <int K, bool RGB, bool DIFF>
+template <bool RGB, bool DIFF>
 static hipError_t go_batch(const BatchParams& bp, int blocks, hipStream_t s)
 {
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, BATCH_BAND_H) : 0;
-    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, s, bp);
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(2, bp.max_band) : 0;
+    const int n = std::max(bp.n_counters, bp.n_clips);
+    hipLaunchKernelGGL(k_batch_reset, dim3((n + 255) / 256), dim3(256), 0, s, bp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rowfuse_batch<K, RGB, DIFF>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, bp);
+    if ((e = allow_row_lds((const void*)k_rowfuse_batch<2, RGB, DIFF>, lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL((k_rowfuse_batch<2, RGB, DIFF>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, bp);
     return hipGetLastError();
 }
 
-hipError_t launch_rowfuse_batch(const BatchParams& bp, int K, bool rgb, bool diff, int blocks, hipStream_t s)
+hipError_t launch_rowfuse_batch(const BatchParams& bp, bool rgb, bool diff, int blocks, hipStream_t s)
 {
-    if (K != 2) return hipErrorInvalidValue;
-    if (rgb) return diff ? go_batch<2, true, true>(bp, blocks, s) : go_batch<2, true, false>(bp, blocks, s);
-    return diff ? go_batch<2, false, true>(bp, blocks, s) : go_batch<2, false, false>(bp, blocks, s);
-}
-
-template <int K, bool RGB, bool DIFF>
-static int occ()
-{
-    int n = 0;
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, BATCH_BAND_H) : 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_rowfuse_batch<K, RGB, DIFF>, ROW_WAVES * 64, lds) !=
-        hipSuccess)
-        return 0;
-    return n;
-}
-
-int rowfuse_batch_blocks_per_cu(int K, bool rgb, bool diff)
-{
-    if (K != 2) return 0;
-    if (rgb) return diff ? occ<2, true, true>() : occ<2, true, false>();
-    return diff ? occ<2, false, true>() : occ<2, false, false>();
+    if (rgb) return diff ? go_batch<true, true>(bp, blocks, s) : go_batch<true, false>(bp, blocks, s);
+    return diff ? go_batch<false, true>(bp, blocks, s) : go_batch<false, false>(bp, blocks, s);
 }
 
 }  // namespace fz

@@ -466,17 +466,17 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowgen(RowParams rp)
     extern __shared__ uint8_t gen_lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int item = blockIdx.x * ROW_WAVES + wave;
-    const RowItem it = row_decompose(item, rp.nstrips, rp.nbands, rp.nchunks, rp.band_h, rp.tt, rp.strip_step);
-    uint8_t* prev = gen_lds + wave * rp.band_h * 64;
+    const RowItem it = row_decompose(item, rp.g.nstrips, rp.g.nbands, rp.g.nchunks, rp.g.band_h, rp.g.tt, rp.g.strip_step);
+    uint8_t* prev = gen_lds + wave * rp.g.band_h * 64;
     if constexpr (I::HAS_NMS) {
         __shared__ PointLists<K, ROW_WAVES> lists;
         lists_begin(lists);
-        if (item >= rp.total) return;
+        if (item >= rp.g.total) return;
         const int held = gen_item<CH, A, B, K>(rp.sp, it, prev, &lists.wave[wave]);
         if (rp.sp.count != nullptr)
-            lists_end(lists, wave, held, min(ROW_WAVES, rp.total - (int)blockIdx.x * ROW_WAVES));
+            lists_end(lists, wave, held, min(ROW_WAVES, rp.g.total - (int)blockIdx.x * ROW_WAVES));
     } else {
-        if (item >= rp.total) return;
+        if (item >= rp.g.total) return;
         (void)gen_item<CH, A, B, K>(rp.sp, it, prev, nullptr);
     }
 }
@@ -487,8 +487,8 @@ hipError_t launch_rowgen_t(const RowParams& rp, hipStream_t s)
     if constexpr (A > B || B >= chain_len(CH) || !group_has_window(CH, A, B)) {
         return hipErrorInvalidValue;
     } else {
-        const int blocks = (rp.total + ROW_WAVES - 1) / ROW_WAVES;
-        const size_t lds = GenInfo<CH, A, B>::DIFF ? (size_t)ROW_WAVES * rp.band_h * 64 : 0;
+        const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
+        const size_t lds = GenInfo<CH, A, B>::DIFF ? (size_t)ROW_WAVES * rp.g.band_h * 64 : 0;
         const hipError_t e = allow_row_lds((const void*)k_rowgen<CH, A, B, K>, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_rowgen<CH, A, B, K>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);

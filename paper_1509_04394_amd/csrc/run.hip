@@ -103,26 +103,26 @@ static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_
         } else if (g.engine == FZ_ENGINE_ROW) {
             RowParams rp{};
             rp.sp = sp;
-            rp.nstrips = g.nstrips;
-            rp.nbands = g.nbands;
-            rp.nchunks = g.nchunks;
-            rp.total = g.nstrips * g.nbands * g.nchunks;
-            rp.band_h = g.tile_h;
-            rp.tt = g.tpb;
+            rp.g.nstrips = g.nstrips;
+            rp.g.nbands = g.nbands;
+            rp.g.nchunks = g.nchunks;
+            rp.g.total = g.nstrips * g.nbands * g.nchunks;
+            rp.g.band_h = g.tile_h;
+            rp.g.tt = g.tpb;
             if (g.row_gen) {
-                rp.strip_step = 64 * g.row_k - 2 * g.halo;
+                rp.g.strip_step = 64 * g.row_k - 2 * g.halo;
                 RowGenFn fn = lookup_rowgen(p.chain, g.cfirst, g.clast);
                 if (!fn) return fail(FZ_E_UNSUPPORTED, "no row kernel compiled for this group");
                 e = fn(rp, s);
             } else {
-                rp.strip_step = 64 * g.row_k - 2 * ROW_HX;
+                rp.g.strip_step = 64 * g.row_k - 2 * ROW_HX;
                 const size_t xb = exchange_bytes(p, g);
                 if (xb > 0 && exchange) {
                     if (!xch || ws_bytes < workspace_bytes(p))
                         return fail(FZ_E_WORKSPACE, "the frame-difference row group needs the exchange workspace");
                     const size_t nb = (size_t)row_boundaries(g.nstrips, g.nbands, g.nchunks);
-                    rp.xmask = (uint32_t*)xch;
-                    rp.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
+                    rp.g.xmask = (uint32_t*)xch;
+                    rp.g.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
                 }
                 e = launch_rowfuse(rp, g.row_k, g.cfirst == 0, g.clast == 8, s);
             }
