@@ -12,12 +12,14 @@ __global__ void k_batch_reset(BatchParams bp)
     if (i < bp.n_clips && bp.clip[i].count != nullptr) *bp.clip[i].count = 0u;
 }
 
-// Zero n words (the frame-boundary arrival counters; a kernel, not a memset,
-// so that it is an ordinary kernel node when a run is captured into a graph).
-__global__ void k_zero_words(uint32_t* p, int n)
+// Zero n words (the frame-boundary arrival counters) and the point count (null:
+// none); a kernel, not a memset, so that it is an ordinary kernel node when a run
+// is captured into a graph.
+__global__ void k_zero_words(uint32_t* p, int n, uint32_t* count)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
+    if (i == 0 && count != nullptr) *count = 0u;
 }
 
 template <int K, bool RGB, bool DIFF>
@@ -25,13 +27,12 @@ static hipError_t go(const RowParams& rp, hipStream_t s)
 {
     const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
     const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.g.band_h) : 0;
-    if (DIFF && rp.g.xcount != nullptr) {
-        const int nb = row_boundaries(rp.g.nstrips, rp.g.nbands, rp.g.nchunks);
-        if (nb > 0) {
-            hipLaunchKernelGGL(k_zero_words, dim3((nb + 255) / 256), dim3(256), 0, s, rp.g.xcount, nb);
-            const hipError_t z = hipGetLastError();
-            if (z != hipSuccess) return z;
-        }
+    const int nb = DIFF && rp.g.xcount != nullptr ? row_boundaries(rp.g.nstrips, rp.g.nbands, rp.g.nchunks) : 0;
+    if (nb > 0 || rp.sp.count != nullptr) {
+        hipLaunchKernelGGL(k_zero_words, dim3(std::max(1, (nb + 255) / 256)), dim3(256), 0, s, rp.g.xcount, nb,
+                           rp.sp.count);
+        const hipError_t z = hipGetLastError();
+        if (z != hipSuccess) return z;
     }
     const hipError_t e = allow_row_lds((const void*)k_rowfuse<K, RGB, DIFF>, lds);
     if (e != hipSuccess) return e;

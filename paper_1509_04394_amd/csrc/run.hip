@@ -71,7 +71,11 @@ static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_
     size_t ck = 0;
     for (const Segment& g : p.segs) ck = std::max(ck, ckpt_bytes(p, g));
     char* xch = d_ws ? (char*)d_ws + slots_bytes(p) + align256(ck) : nullptr;
-    if (d_count && p.has_nms) {
+    // the point count is reset here, or by the Harris row kernel's launch with its own counters
+    bool row_resets = false;
+    for (const Segment& g : p.segs)
+        row_resets |= !p.generic && g.engine == FZ_ENGINE_ROW && !g.row_gen;  // such a group holds the suppression stage
+    if (d_count && p.has_nms && !row_resets) {
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d_count);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FZ_E_HIP, std::string("zeroing the point count: ") + hipGetErrorString(e));
