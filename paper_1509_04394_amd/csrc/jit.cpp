@@ -129,8 +129,13 @@ std::string jit_source(const fz_plan& p, const Segment& g)
     // registers ist<j>[k][q] (k: its k-th group), restored from the
     // checkpoint of the run before.
     o << "    constexpr int NLV = (NV + 255) / 256, NPF = " << (u8 ? "NLV" : "4 * NLV") << ";\n"
-         "    const int a0 = ox - S;\n"
-         "    unsigned int pf[NPF];  // the next box: four u8 cells or one f32 cell per word\n";
+         "    unsigned int pf[NPF];  // the next box: four u8 cells or one f32 cell per word\n"
+         "    int at[NLV];  // each group's first cell in its frame, its row clamped\n"
+         "#pragma unroll\n"
+         "    for (int k = 0; k < NLV; ++k) {\n"
+         "        const int it = threadIdx.x + 256 * k, ly = it / ND, kd = it - ly * ND;\n"
+         "        at[k] = clampi(oy + ly, 0, H - 1) * W + ox - S + 4 * kd;\n"
+         "    }\n";
     int n_lead_iir = 0;
     for (int j = 0; j < lead; ++j)
         if (st[j].kind == G_IIR) o << "    double ist" << n_lead_iir++ << "[NLV][4];\n";
@@ -175,11 +180,9 @@ std::string jit_source(const fz_plan& p, const Segment& g)
              "            for (int k = 0; k < NLV; ++k) {\n"
              "                const int it = threadIdx.x + 256 * k;\n"
              "                if (it < NV) {\n"
-             "                    const int ly = it / ND, kd = it - ly * ND;\n"
-             "                    const size_t rb = gb + (size_t)clampi(oy + ly, 0, H - 1) * W;\n"
              "                    if (xin) {\n"
              "                        const "
-          << vt << " w = *(const " << vt << "*)(in + rb + a0 + 4 * kd);\n";
+          << vt << " w = *(const " << vt << "*)(in + gb + at[k]);\n";
         if (u8)
             q << "                        pf[k] = w;\n";
         else
@@ -187,13 +190,13 @@ std::string jit_source(const fz_plan& p, const Segment& g)
                  "                        pf[4 * k + 1] = __float_as_uint(w.y);\n"
                  "                        pf[4 * k + 2] = __float_as_uint(w.z);\n"
                  "                        pf[4 * k + 3] = __float_as_uint(w.w);\n";
-        q << "                    } else {\n";
-        if (u8)
-            q << "                        unsigned int w = 0;\n";
+        q << "                    } else {\n"
+             "                        const int ly = it / ND, kd = it - ly * ND;\n"
+             "                        const size_t rb = gb + (size_t)clampi(oy + ly, 0, H - 1) * W;\n";
+        if (u8) q << "                        unsigned int w = 0;\n";
         q << "#pragma unroll\n"
              "                        for (int q = 0; q < 4; ++q) {\n"
-             "                            const int lx = 4 * kd + q - S;\n"
-             "                            if (lx < 0 || lx >= RW) continue;\n";
+             "                            const int lx = 4 * kd + q - S;\n";
         if (u8)
             q << "                            w |= (unsigned int)in[rb + clampi(ox + lx, 0, W - 1)] << (8 * q);\n";
         else
@@ -214,8 +217,14 @@ std::string jit_source(const fz_plan& p, const Segment& g)
          "        const bool first = f == 0;\n"
          "        const size_t fbase = (size_t)f * P;\n"
          "        float* dst = lds + "
-      << st[lead].buf << " + (f % " << st[lead].slots << ") * CELLS;\n"
-      << "#pragma unroll\n"
+      << st[lead].buf << " + (f % " << st[lead].slots << ") * CELLS;\n";
+    // The box's groups go to LDS whole, S cells right of the box's cell 0 (a row's
+    // pitch holds them), so no cell is tested, and each group's place in the
+    // frame is formed once: 800x600x1000 u8, the paper's five kernels, 1151 us
+    // -> 1054 us; look-back chain at 800x600x200 589 us -> 539 us.  (Forcing 128
+    // registers, a wavefront more a SIMD, runs 1142 us; a copy of the loop for
+    // the clip's first frame, without the select, 1370 us at more registers.)
+    o << "#pragma unroll\n"
          "        for (int k = 0; k < NLV; ++k) {\n"
          "            const int it = threadIdx.x + 256 * k;\n"
          "            if (it < NV) {\n"
@@ -223,10 +232,10 @@ std::string jit_source(const fz_plan& p, const Segment& g)
     for (int q = 0; q < 4; ++q) {
         std::string ls = lead_stmts;
         for (size_t pos; (pos = ls.find("[k][Q]")) != std::string::npos;) ls.replace(pos, 6, "[k][" + std::to_string(q) + "]");
-        o << "                if (" << (q < S ? "kd > 0 && " : "") << "4 * kd + " << q - S << " < RW) {\n"
+        o << "                {\n"
           << "                    float v = " << (u8 ? std::string(vx[q]) : "__uint_as_float(pf[4 * k + " + std::to_string(q) + "])")
           << ";\n"
-          << ls << "                    dst[ly * LP + 4 * kd + " << q - S << "] = v;\n                }\n";
+          << ls << "                    dst[ly * LP + 4 * kd + " << q << "] = v;\n                }\n";
     }
     o << "            }\n"
          "        }\n"
@@ -274,7 +283,7 @@ std::string jit_source(const fz_plan& p, const Segment& g)
              "#pragma unroll\n"
              "                    for (int tau = 0; tau <= RT; ++tau) {\n"
              "                        const float* src = lds + "
-          << s.buf << " + (max(f - tau, 0) % " << s.slots
+          << s.buf << (i == lead ? " + S" : "") << " + (max(f - tau, 0) % " << s.slots
           << ") * CELLS;\n"
              "#pragma unroll\n"
              "                        for (int v = -RY; v < GR + RY; ++v) {\n"
