@@ -73,12 +73,15 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Sum over the 16 lanes of a row (every lane gets it).
+// Sum over the 16 lanes of a row (every lane gets it), by rotations within it.
+template <int N>
+__device__ __forceinline__ float add_rotated(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + N, 0xf, 0xf, true));  // row_ror:N
+}
 __device__ __forceinline__ float sum16(float v)
 {
-#pragma unroll
-    for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
-    return v;
+    return add_rotated<1>(add_rotated<2>(add_rotated<4>(add_rotated<8>(v))));
 }
 
 template <bool TRAIN>
