@@ -61,7 +61,7 @@ static inline __host__ __device__ MlpOffsets mlp_offsets(int F)
 // (latency; the 246 MFLOP of a step of 8192 samples are 1.6 us at the FP32
 // matrix rate).  32 samples a tile give 8192 samples 256 workgroups, one a CU.
 // Measured, a step of 8192 samples of 20 features with its reduction and Adam:
-// 18.3 us; 88.7 us with one multiply-add a lane at a time, operands read from
+// 17.1 us; 88.7 us with one multiply-add a lane at a time, operands read from
 // LDS, a forward and a backward launch with the activations in between in
 // memory, and the partial gradients added by one dependent chain (34 us of it).
 constexpr int MLP_XP = 36, MLP_HP = 68;  // LDS row pitches (floats)
@@ -132,28 +132,37 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp(const float* __restrict__ p
         __syncthreads();
         f32x4 h1[RT], h2[RT];
         // layer 1: h1 = relu(x W1^T + b1)
+        // (the row tiles' sums in turn: one's latency hides the other's)
+        f32x4 a[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) a[r] = f32x4{b1, b1, b1, b1};
+#pragma unroll
+        for (int k = 0; k < MLP_FMAX / 4; ++k)
+            if (4 * k < F) {
+#pragma unroll
+                for (int r = 0; r < RT; ++r) a[r] = mfma4(xs[16 * r + c][4 * k + q], w1[k], a[r]);
+            }
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
-            f32x4 a = {b1, b1, b1, b1};
-#pragma unroll
-            for (int k = 0; k < MLP_FMAX / 4; ++k)
-                if (4 * k < F) a = mfma4(xs[16 * r + c][4 * k + q], w1[k], a);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                h1[r][e] = a[e] > 0.0f ? a[e] : 0.0f;
+                h1[r][e] = a[r][e] > 0.0f ? a[r][e] : 0.0f;
                 h1s[16 * r + 4 * q + e][j] = h1[r][e];
             }
         }
         __syncthreads();
         // layer 2 and this wavefront's share of the output layer
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            f32x4 a = {b2, b2, b2, b2};
+        for (int r = 0; r < RT; ++r) a[r] = f32x4{b2, b2, b2, b2};
 #pragma unroll
-            for (int k = 0; k < 16; ++k) a = mfma4(h1s[16 * r + c][4 * k + q], w2[k], a);
+        for (int k = 0; k < 16; ++k)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) a[r] = mfma4(h1s[16 * r + c][4 * k + q], w2[k], a[r]);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                h2[r][e] = a[e] > 0.0f ? a[e] : 0.0f;
+                h2[r][e] = a[r][e] > 0.0f ? a[r][e] : 0.0f;
                 const float v = sum16(w3 * h2[r][e]);
                 if (c == 0) yp[w][16 * r + 4 * q + e] = v;
             }
@@ -189,13 +198,16 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp(const float* __restrict__ p
                     for (int k = 0; k < 4; ++k) g2[k] = mfma4(d2[r][e], h1s[16 * r + 4 * q + e][16 * k + c], g2[k]);
             // dz1 = (dz2 W2) where h1 > 0, then gW1 += dz1^T x
 #pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                f32x4 a = {};
+            for (int r = 0; r < RT; ++r) a[r] = f32x4{};
 #pragma unroll
-                for (int k = 0; k < 16; ++k) a = mfma4(d2s[16 * r + c][4 * k + q], w2t[k], a);
+            for (int k = 0; k < 16; ++k)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) a[r] = mfma4(d2s[16 * r + c][4 * k + q], w2t[k], a[r]);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float d1 = h1[r][e] > 0.0f ? a[e] : 0.0f;
+                    const float d1 = h1[r][e] > 0.0f ? a[r][e] : 0.0f;
                     gb1 += d1;
 #pragma unroll
                     for (int k = 0; k < 2; ++k) g1[k] = mfma4(d1, xs[16 * r + 4 * q + e][16 * k + c], g1[k]);
