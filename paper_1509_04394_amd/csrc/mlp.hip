@@ -114,6 +114,17 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp(const float* __restrict__ p
     const int tiles = (n + MLP_ROWS - 1) / MLP_ROWS;
     for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
         const int s0 = t * MLP_ROWS;
+        // the rows past the last sample have no activations: those of a sample of
+        // zeros may be infinite where the real ones are not, and 0 * inf in a
+        // gradient sum is NaN
+        auto blank = [&](f32x4(&z)[RT]) {
+            if (!TRAIN || s0 + MLP_ROWS <= n) return;
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (s0 + 16 * r + 4 * q + e >= n) z[r][e] = 0.0f;
+        };
 #pragma unroll
         for (int i = tid; i < MLP_ROWS * MLP_FMAX; i += MLP_THREADS) {
             const int s = i / MLP_FMAX, f = i % MLP_FMAX;
@@ -142,6 +153,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp(const float* __restrict__ p
 #pragma unroll
                 for (int r = 0; r < RT; ++r) a[r] = mfma4(xs[16 * r + c][4 * k + q], w1[k], a[r]);
             }
+        blank(a);
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
 #pragma unroll
@@ -158,6 +170,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp(const float* __restrict__ p
         for (int k = 0; k < 16; ++k)
 #pragma unroll
             for (int r = 0; r < RT; ++r) a[r] = mfma4(h1s[16 * r + c][4 * k + q], w2[k], a[r]);
+        blank(a);
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
 #pragma unroll
