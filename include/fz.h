@@ -293,9 +293,10 @@ fz_status fz_run_chain(const fz_plan* plan, const void* d_in, void* d_out, fz_po
  *   - Limit: plans whose fz_workspace_bytes() exceeds FZ_STATIC_WORKSPACE_BYTES
  *     (64 MiB) are refused with FZ_E_WORKSPACE before anything is launched or
  *     any device is touched.  The words of the frame-boundary exchange do not
- *     count: where only they pass the limit (the fused 800x600x1000 RGB chain
- *     at its planned 2-frame runs), each run recomputes the frame before it
- *     instead.
+ *     count: where they do not fit in what is left of the array (the fused
+ *     640x480x1000 chain at its planned 1-frame runs), the run takes longer
+ *     frame runs, or each run recomputes the frame before it, whichever the
+ *     sizing model finds faster.
  *   - Each GPU the library runs on holds its own 64 MiB array from the first
  *     call on that device (which looks its address up) until the process ends.
  *   - Every call on one GPU shares that GPU's array and leaves its contents

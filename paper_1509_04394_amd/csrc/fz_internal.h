@@ -98,12 +98,10 @@ double partition_dp(const double* cost, int n, std::vector<int>& seg_last);
 // Device side (run.hip)
 fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
                    uint32_t cap, void* d_ws, size_t ws_bytes, void* stream);
-// The same with frame-difference row groups that recompute the frame before each
-// run (workspace_bytes_no_exchange() is enough).
-fz_status run_plan_no_exchange(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream);
 size_t workspace_bytes(const fz_plan& p);
-size_t workspace_bytes_no_exchange(const fz_plan& p);
+// The least a run can do with: without the words of the frame-boundary exchange
+// (run_plan then picks the frame runs by the room that is left, see row_run).
+size_t workspace_bytes_least(const fz_plan& p);
 
 // Measured prices (measure.hip)
 size_t measure_workspace_bytes(const fz_plan& p);

@@ -112,6 +112,12 @@ constexpr int ROW_DIFF_MAX_BAND = 256;
 struct RowShape {
     int band_h, tt;
 };
+// The model's time of `items` items of bh rows that march `frames` frames.
+inline double row_time(int bh, double frames, double items, int slots)
+{
+    const double r = items / (double)slots, w = (bh + 8.9) * frames + 9.7;
+    return w * (r + 0.083 * (std::ceil(r) - r) + 0.9);
+}
 inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic)
 {
     if (req_h > 0 && diff && std::min(req_h, H) > ROW_DIFF_MAX_BAND) return RowShape{0, 0};
@@ -149,9 +155,7 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
                 const double r = (double)items / (double)fit;
                 cost = (double)items * (bh + 2 * ROW_HX) * (t + 0.45 * xch) * (1.0 + 1.0 / r) * ((double)slots / (double)fit);
             } else {
-                const double r = (double)items / (double)slots;
-                const double w = (bh + 8.9) * (t + 0.15 * xch) + 9.7;
-                cost = w * (r + 0.083 * (std::ceil(r) - r) + 0.9);
+                cost = row_time(bh, t + 0.15 * xch, (double)items, slots);
             }
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
@@ -161,6 +165,33 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
         }
     }
     return best;
+}
+
+// How a frame-difference group of the Harris row kernel runs in a workspace with
+// `room` bytes for its exchange: as planned where the words fit; else in the run
+// (the planned one times a power of two) of least modelled time, each item
+// recomputing the frame before its run where the words do not fit at that run
+// either.  In the static 64 MiB, 640x480x1000 gray, planned at one frame a run,
+// takes 587 us with two-frame runs (988 us recomputing at one), 800x600x700 RGB
+// 728 us (1206 us).
+struct RowRun {
+    int tt, nchunks;
+    bool exchange;
+};
+inline RowRun row_run(size_t room, int T, int nstrips, int nbands, int band_h, int K, int tt, int slots)
+{
+    RowRun best{};
+    double best_time = -1.0;
+    for (int t = tt;; t = t > T / 2 ? T : 2 * t) {
+        const int n = (T + t - 1) / t;
+        const bool fits = row_exchange_bytes(nstrips, nbands, n, band_h, K) <= room;
+        const double time = row_time(band_h, t + (n == 1 ? 0.0 : fits ? 0.15 : 1.0), (double)nstrips * nbands * n, slots);
+        if (best_time < 0.0 || time < best_time) {
+            best = RowRun{t, n, fits && n > 1};
+            best_time = time;
+        }
+        if (fits) return best;  // n == 1 needs no words
+    }
 }
 
 }  // namespace fz

@@ -54,23 +54,22 @@ size_t workspace_bytes(const fz_plan& p)
     return slots_bytes(p) + align256(ck) + xb;
 }
 
-size_t workspace_bytes_no_exchange(const fz_plan& p)
+size_t workspace_bytes_least(const fz_plan& p)
 {
     size_t ck = 0;
     for (const Segment& g : p.segs) ck = std::max(ck, ckpt_bytes(p, g));
     return slots_bytes(p) + align256(ck);
 }
 
-static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream, bool exchange)
+fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
+                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
 {
     (void)hipGetLastError();  // drop an error latched by earlier, unrelated runtime calls
     hipStream_t s = (hipStream_t)stream;
     const size_t slot = p.segs.size() > 1 ? align256(slots_bytes(p) / (p.segs.size() > 2 ? 2 : 1)) : 0;
     void* ckpt = d_ws ? (void*)((char*)d_ws + slots_bytes(p)) : nullptr;
-    size_t ck = 0;
-    for (const Segment& g : p.segs) ck = std::max(ck, ckpt_bytes(p, g));
-    char* xch = d_ws ? (char*)d_ws + slots_bytes(p) + align256(ck) : nullptr;
+    const size_t least = workspace_bytes_least(p);  // the exchange words come after these bytes
+    const size_t room = d_ws && ws_bytes > least ? ws_bytes - least : 0;
     // the point count is reset here, or by the Harris row kernel's launch with its own counters
     bool row_resets = false;
     for (const Segment& g : p.segs)
@@ -120,13 +119,18 @@ static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_
                 e = fn(rp, s);
             } else {
                 rp.g.strip_step = 64 * g.row_k - 2 * ROW_HX;
-                const size_t xb = exchange_bytes(p, g);
-                if (xb > 0 && exchange) {
-                    if (!xch || ws_bytes < workspace_bytes(p))
-                        return fail(FZ_E_WORKSPACE, "the frame-difference row group needs the exchange workspace");
-                    const size_t nb = (size_t)row_boundaries(g.nstrips, g.nbands, g.nchunks);
-                    rp.g.xmask = (uint32_t*)xch;
-                    rp.g.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
+                if (exchange_bytes(p, g) > 0) {
+                    const RowRun r = row_run(room, p.T, g.nstrips, g.nbands, g.tile_h, g.row_k, g.tpb,
+                                             row_slots(g.row_k, g.cfirst == 0));
+                    rp.g.tt = r.tt;
+                    rp.g.nchunks = r.nchunks;
+                    rp.g.total = g.nstrips * g.nbands * r.nchunks;
+                    if (r.exchange) {
+                        char* xch = (char*)d_ws + least;
+                        const size_t nb = (size_t)row_boundaries(g.nstrips, g.nbands, r.nchunks);
+                        rp.g.xmask = (uint32_t*)xch;
+                        rp.g.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
+                    }
                 }
                 e = launch_rowfuse(rp, g.row_k, g.cfirst == 0, g.clast == 8, s);
             }
@@ -141,18 +145,6 @@ static fz_status run_groups(const fz_plan& p, const void* d_in, void* d_out, fz_
         cur_in = sp.out;
     }
     return FZ_OK;
-}
-
-fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                   uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
-{
-    return run_groups(p, d_in, d_out, d_points, d_count, cap, d_ws, ws_bytes, stream, true);
-}
-
-fz_status run_plan_no_exchange(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_points, uint32_t* d_count,
-                               uint32_t cap, void* d_ws, size_t ws_bytes, void* stream)
-{
-    return run_groups(p, d_in, d_out, d_points, d_count, cap, d_ws, ws_bytes, stream, false);
 }
 
 }  // namespace fz

@@ -59,22 +59,19 @@ fz_status fz_run_chain_static(const fz_plan* plan, const void* d_in, void* d_out
     if (!plan || !d_in || !d_out) return fail(FZ_E_INVALID, "fz_run_chain_static: null plan or buffer");
     if (point_capacity > 0 && !d_points)
         return fail(FZ_E_INVALID, "fz_run_chain_static: capacity without a point buffer");
-    // a frame-difference row group whose exchange words alone pass the limit
-    // runs without them, each item recomputing the frame before its run
-    size_t need = workspace_bytes(*plan);
-    const bool exchange = need <= FZ_STATIC_WORKSPACE_BYTES;
-    if (!exchange) need = workspace_bytes_no_exchange(*plan);
+    // (a frame-difference row group takes what room is left for its exchange words)
+    const size_t need = workspace_bytes_least(*plan);
     if (need > FZ_STATIC_WORKSPACE_BYTES)
         return fail(FZ_E_WORKSPACE, "fz_run_chain_static: the plan needs " + std::to_string(need) +
                                         " bytes of workspace, more than the static " +
                                         std::to_string((size_t)FZ_STATIC_WORKSPACE_BYTES) + "; use fz_run_chain");
     void* ws = nullptr;
-    if (need > 0) {
+    if (workspace_bytes(*plan) > 0) {
         const fz_status st = scratch_address(&ws);
         if (st != FZ_OK) return st;
     }
-    return (exchange ? run_plan : run_plan_no_exchange)(*plan, d_in, d_out, d_points, d_point_count, point_capacity, ws,
-                                                        need > 0 ? FZ_STATIC_WORKSPACE_BYTES : 0, stream);
+    return run_plan(*plan, d_in, d_out, d_points, d_point_count, point_capacity, ws, ws ? FZ_STATIC_WORKSPACE_BYTES : 0,
+                    stream);
 }
 
 }  // extern "C"
