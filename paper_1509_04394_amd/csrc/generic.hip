@@ -626,6 +626,8 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_gmarch(const GParams)
 // Reading the stage list for every frame, with a scalar load's latency each
 // time and two wavefronts a SIMD to hide it, bound the kernel: 800x600x1000 u8
 // with a checkpoint every 16 frames took 329 us and takes 161 us.
+// Without RAW its input is f32: a test of the type at every load kept the loads
+// from being in flight together (192x432x600 f32 333 us; now 147).
 template <int PX, int D, bool CKPT, bool ONE, bool RAW = false, bool SINGLE = false>
 __global__ __launch_bounds__(BLOCK_THREADS) void k_gstream_t(const GParams p)
 {
@@ -651,7 +653,7 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_gstream_t(const GParams p)
             if constexpr (RAW) {
                 raw[d] = *(const uint32_t*)((const uint8_t*)p.in + gi);
             } else if constexpr (PX == 4) {
-                if (p.in_u8) {
+                if (!SINGLE && p.in_u8) {
                     const uchar4 q = *(const uchar4*)((const uint8_t*)p.in + gi);
                     v[d][0] = q.x;
                     v[d][1] = q.y;
