@@ -667,9 +667,10 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_stream(SegParams p)
 {
     static_assert(chain_op(CH, B) != FZ_OP_FRAMEDIFF || A == B, "a streamed frame difference reads its u8 input as it is");
     const size_t plane = (size_t)p.W * p.H, vol = plane * p.T;
-    const size_t i = ((size_t)blockIdx.x * BLOCK_THREADS + threadIdx.x) * 4;
-    if (i + 4 <= vol)
-        stream_px<CH, A, B, 4>(p, plane, vol, i);
+    const size_t wg = (size_t)blockIdx.y * STREAM_ROW + blockIdx.x;
+    const size_t i = (wg * BLOCK_THREADS + threadIdx.x) * STREAM_PX;
+    if (i + STREAM_PX <= vol)
+        stream_px<CH, A, B, STREAM_PX>(p, plane, vol, i);
     else
         for (size_t j = i; j < vol; ++j) stream_px<CH, A, B, 1>(p, plane, vol, j);
 }
@@ -681,9 +682,9 @@ hipError_t launch_group(const SegParams& p, int tile, hipStream_t s)
     if constexpr (A > B || B >= chain_len(CH) || A < 0) {
         return hipErrorInvalidValue;
     } else if constexpr (!group_has_window(CH, A, B)) {
-        const size_t blocks = ((size_t)p.W * p.H * p.T + 4 * BLOCK_THREADS - 1) / (4 * BLOCK_THREADS);
-        if (blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((k_stream<CH, A, B>), dim3((unsigned)blocks), dim3(BLOCK_THREADS), 0, s, p);
+        const StreamGrid g = stream_grid((unsigned long long)p.W * p.H * p.T);
+        if (g.y > 65535u) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((k_stream<CH, A, B>), dim3(g.x, g.y), dim3(BLOCK_THREADS), 0, s, p);
         return hipGetLastError();
     } else {
         auto go = [&](auto kern, int tw, int th) {
