@@ -564,14 +564,23 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_group(SegParams p)
 
 // Groups without a window stage: one pass over the pixels.  Point stages need
 // no coordinates, so a clip is a flat array of W*H*T pixels per channel; each
-// thread takes 4 consecutive pixels with vector loads and stores, the last
+// thread takes 4 or 16 consecutive pixels with vector loads and stores, the last
 // thread the remainder.  The vectors are declared at their element's
 // alignment: an odd frame size or an odd buffer puts them anywhere, which the
 // memory path takes.  Bound by memory: the five point stages of the Harris chain
 // at 641x479x75 took 261 us with one pixel a thread (where a frame was no
 // multiple of four pixels) and take 222.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32u __attribute__((aligned(1)));
+template <int N>
+using u8s = uint32_t __attribute__((ext_vector_type(N / 4), aligned(1)));  // N bytes
+// Pixels a thread: 16 where a pixel is one byte in and out (with four the
+// workgroups, not memory, bound the frame difference: 800x600x500 155 us, now 99).
+template <int CH, int A, int B>
+constexpr int stream_v()
+{
+    constexpr OpInfo a = op_info(chain_op(CH, A)), b = op_info(chain_op(CH, B));
+    return a.in_ch * dt_bytes(a.in_dt) == 1 && b.out_ch * dt_bytes(b.out_dt) == 1 ? 16 : 4;
+}
 template <int CH, int A, int B, int V>
 __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, size_t vol, size_t i)
 {
@@ -584,8 +593,7 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, size
         if constexpr (oa.op == FZ_OP_RGB2GRAY) {
             const uint8_t* s = (const uint8_t*)p.in + 3 * off;
             if constexpr (V == 4) {
-                const u32u* w = (const u32u*)s;
-                const uint32_t b[3] = {w[0], w[1], w[2]};
+                const u8s<12> b = *(const u8s<12>*)s;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) dst[k / 3][k % 3] = (float)((b[k / 4] >> (8 * (k % 4))) & 255u);
             } else {
@@ -593,10 +601,10 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, size
             }
         } else if constexpr (oa.in_dt == FZ_U8) {
             const uint8_t* s = (const uint8_t*)p.in + off;
-            if constexpr (V == 4) {
-                const uint32_t w = *(const u32u*)s;
+            if constexpr (V > 1) {
+                const u8s<V> w = *(const u8s<V>*)s;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) dst[k][0] = (float)((w >> (8 * k)) & 255u);
+                for (int k = 0; k < V; ++k) dst[k][0] = (float)((w[k / 4] >> (8 * (k % 4))) & 255u);
             } else {
                 dst[0][0] = (float)s[0];
             }
@@ -619,30 +627,24 @@ __device__ __forceinline__ void stream_px(const SegParams& p, size_t plane, size
     load(i, v);
     if constexpr (TEMPORAL) {
         // the frame before; the clip's first frame differs from itself
+        // (one load at a selected place, no branch: in flight with the first)
         float u[V][3];
-        if (i >= plane) {
-            load(i - plane, u);
-        } else {
-            const size_t at = i + V > plane ? i + V - plane : 0;  // pixels of the second frame
+        load(i >= plane ? i - plane : i, u);
+        if (i < plane && i + V > plane) {  // the thread with pixels of the first two frames
 #pragma unroll
-            for (int k = 0; k < V; ++k) {
-                u[k][0] = v[k][0];
-                if (k + (int)at >= V) {
-                    const size_t j = i + k - plane;
-                    u[k][0] = (float)((const uint8_t*)p.in)[j];
-                }
-            }
+            for (int k = 0; k < V; ++k)
+                if (i + k >= plane) u[k][0] = (float)((const uint8_t*)p.in)[i + k - plane];
         }
 #pragma unroll
         for (int k = 0; k < V; ++k) v[k][0] = (float)framediff((uint32_t)v[k][0], (uint32_t)u[k][0]);
     }
     if constexpr (ob.out_dt == FZ_U8) {
         uint8_t* d = (uint8_t*)p.out + i;
-        if constexpr (V == 4) {
-            uint32_t w = 0;
+        if constexpr (V > 1) {
+            u8s<V> w = {};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) w |= ((uint32_t)v[k][0] & 255u) << (8 * k);
-            *(u32u*)d = w;
+            for (int k = 0; k < V; ++k) w[k / 4] |= ((uint32_t)v[k][0] & 255u) << (8 * (k % 4));
+            *(u8s<V>*)d = w;
         } else {
             d[0] = (uint8_t)(uint32_t)v[0][0];
         }
@@ -667,10 +669,11 @@ __global__ __launch_bounds__(BLOCK_THREADS) void k_stream(SegParams p)
 {
     static_assert(chain_op(CH, B) != FZ_OP_FRAMEDIFF || A == B, "a streamed frame difference reads its u8 input as it is");
     const size_t plane = (size_t)p.W * p.H, vol = plane * p.T;
+    constexpr int V = stream_v<CH, A, B>();
     const size_t wg = (size_t)blockIdx.y * STREAM_ROW + blockIdx.x;
-    const size_t i = (wg * BLOCK_THREADS + threadIdx.x) * STREAM_PX;
-    if (i + STREAM_PX <= vol)
-        stream_px<CH, A, B, STREAM_PX>(p, plane, vol, i);
+    const size_t i = (wg * BLOCK_THREADS + threadIdx.x) * V;
+    if (i + V <= vol)
+        stream_px<CH, A, B, V>(p, plane, vol, i);
     else
         for (size_t j = i; j < vol; ++j) stream_px<CH, A, B, 1>(p, plane, vol, j);
 }
@@ -682,7 +685,7 @@ hipError_t launch_group(const SegParams& p, int tile, hipStream_t s)
     if constexpr (A > B || B >= chain_len(CH) || A < 0) {
         return hipErrorInvalidValue;
     } else if constexpr (!group_has_window(CH, A, B)) {
-        const StreamGrid g = stream_grid((unsigned long long)p.W * p.H * p.T);
+        const StreamGrid g = stream_grid((unsigned long long)p.W * p.H * p.T, stream_v<CH, A, B>());
         if (g.y > 65535u) return hipErrorInvalidConfiguration;
         hipLaunchKernelGGL((k_stream<CH, A, B>), dim3(g.x, g.y), dim3(BLOCK_THREADS), 0, s, p);
         return hipGetLastError();

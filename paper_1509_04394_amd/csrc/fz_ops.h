@@ -156,16 +156,16 @@ FZ_HD constexpr int tile_h(int t) { return t == 0 ? 16 : (t == 1 ? 32 : 32); }
 
 constexpr int BLOCK_THREADS = 256;
 
-// Grid of a streaming pass over px pixels of four a thread.  A dimension holds
-// fewer than 2^32 threads: past 2^20 workgroups (2^30 pixels) rows of that many
+// Grid of a streaming pass over px pixels of v a thread.  A dimension holds
+// fewer than 2^32 threads: past 2^20 workgroups rows of that many
 // along y.  (Threads that stride over the clip instead cost 3% at 800x600x64.)
-constexpr int STREAM_PX = 4, STREAM_ROW = 1 << 20;
+constexpr int STREAM_ROW = 1 << 20;
 struct StreamGrid {
     unsigned x, y;
 };
-FZ_HD constexpr StreamGrid stream_grid(unsigned long long px)
+FZ_HD constexpr StreamGrid stream_grid(unsigned long long px, int v)
 {
-    const unsigned long long per = (unsigned long long)STREAM_PX * BLOCK_THREADS, n = (px + per - 1) / per;
+    const unsigned long long per = (unsigned long long)v * BLOCK_THREADS, n = (px + per - 1) / per;
     return n <= STREAM_ROW ? StreamGrid{(unsigned)n, 1u}
                            : StreamGrid{(unsigned)STREAM_ROW, (unsigned)((n + STREAM_ROW - 1) / STREAM_ROW)};
 }

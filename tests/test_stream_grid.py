@@ -1,26 +1,27 @@
 """Streaming passes over long clips: the launch's grid (host arithmetic) and the pixels
-of clips past one row of the grid, and past the 2^34 pixels (4 a thread) that one grid
-dimension could hold."""
+of clips past one row of the grid, and past the 2^34 pixels that one grid dimension
+could hold at 4 a thread."""
 import pytest
 
 from paper_1509_04394_amd import fz
 from tests import hostcpp
 
 
-def test_grid_stays_within_a_dimension(tmp_path):
+@pytest.mark.parametrize("v", [4, 16])  # pixels a thread
+def test_grid_stays_within_a_dimension(tmp_path, v):
     sizes = [1, 4, 1023, 1024, 1025, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, 480000 * 35791, 1 << 34, (1 << 34) + 5, 1 << 40]
     out = hostcpp.run(tmp_path, ["fz_ops.h"], "".join(
-        f'printf("%u %u %d\\n", stream_grid({n}ull).x, stream_grid({n}ull).y, BLOCK_THREADS);\n' for n in sizes))
+        f'printf("%u %u %d\\n", stream_grid({n}ull, {v}).x, stream_grid({n}ull, {v}).y, BLOCK_THREADS);\n' for n in sizes))
     for n, line in zip(sizes, out):
         x, y, threads = map(int, line.split())
         assert 1 <= x <= 1 << 20 and 1 <= y and x * threads < 1 << 32  # threads a grid dimension can hold
         assert y == 1 or x == 1 << 20  # rows of one length, which the kernel multiplies by
         # the clip is covered, with less than a row to spare
-        assert x * y * threads * 4 >= n and (x * (y - 1) if y > 1 else x - 1) * threads * 4 < n
+        assert x * y * threads * v >= n and (x * (y - 1) if y > 1 else x - 1) * threads * v < n
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("op,T", [("framediff", 2240), ("rgb2gray", 2240), ("framediff", 35800)])
+@pytest.mark.parametrize("op,T", [("framediff", 2240), ("rgb2gray", 2240), ("framediff", 35800), ("rgb2gray", 35800)])
 def test_pixels_past_one_row_of_the_grid(op, T):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
