@@ -99,10 +99,15 @@ constexpr int ROW_DIFF_MAX_BAND = 256;
 // 16 rows 30.0 us, 4 rows 21.9; 800x600x200 RGB: 30 x 2 269 us, 67 x 1 246).
 //
 // Generic row kernel: without a frame difference, the height nearest 18 rows
-// that divides the frame evenly, or 14 where that gives under two rounds.  (A
-// sweep over eight groups x eight clips is flat and memory-bound around these:
-// on clips over 2 Mpixel they are 4% from each case's best on average, the model
-// that follows 10%; on smaller ones 9% and 12%.)  With one, the total work,
+// that divides the frame evenly; under two rounds, of the heights nearest 14, 15
+// and 16 the one with the fewest rows one after another on the compute unit that
+// gets the most workgroups.  (A sweep over eight groups x eight clips is flat and
+// memory-bound around 18: on clips over 2 Mpixel it is 4% from each case's best on
+// average, the model that follows 10%.  On fourteen smaller clips x seventeen
+// groups, 14 alone was up to 20% slower than 16 where it gave a compute unit a
+// third workgroup: 333x251x40 gray conversion to products 21.0 us, 17.0 at 15
+// rows; at 192x432x64 14 rows are 7% faster.  The rule is 14% from the sweep's
+// best there, 14 alone 16%, the model that follows 19%.)  With one, the total work,
 // items x (b + 12) x (t + 0.45), times (1 + 1/r), bands from 16 rows on.
 // Explicit requests (> 0)
 // are kept as given, except that a frame run longer than the video is the
@@ -127,7 +132,14 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
             return (H + nb - 1) / nb;
         };
         int bh = even(18);
-        if ((double)nstrips * ((H + bh - 1) / bh) * T < 2.0 * slots) bh = even(14);
+        auto items = [&](int rows) { return (long long)nstrips * ((H + rows - 1) / rows) * T; };
+        if (items(bh) < 2LL * slots) {
+            // rows one after another on the compute unit with the most workgroups
+            auto chain = [&](int rows) { return rows * ((items(rows) + 256 * ROW_WAVES - 1) / (256 * ROW_WAVES)); };
+            bh = even(14);
+            for (int rows : {15, 16})
+                if (chain(even(rows)) < chain(bh)) bh = even(rows);
+        }
         return RowShape{bh, req_tt > 0 ? std::min(req_tt, T) : 1};
     }
     RowShape best{0, 0};
