@@ -169,7 +169,10 @@ typedef struct fz_segment_info {
     int32_t tile_w, tile_h;         /* output box x, y (Sec. V, Fig. 3); ROW: strip span, band rows */
     int32_t frames_per_block;       /* output box t */
     int32_t halo, halo_t;           /* input-box growth per side in x/y, and in frames (Sec. VI-C) */
-    int32_t lds_bytes;              /* on-chip memory of one workgroup */
+    int32_t lds_bytes;              /* on-chip memory of one workgroup; ROW: a byte a lane and band row of the
+                                       mask a frame-difference group keeps, else 0 (the kernel holds packed
+                                       masks and, with the suppression stage, lists of points instead; the
+                                       budget is held against both) */
     int32_t streaming;              /* 1 = no window stage: one pass, no on-chip staging */
     int32_t engine;                 /* FZ_ENGINE_TILE, FZ_ENGINE_ROW or FZ_ENGINE_STREAM */
     double bytes_per_px;            /* compulsory global-memory bytes per output pixel */

@@ -16,7 +16,7 @@ static bool batch_one_launch(const fz_plan& p, const fz_clip* clips, int n)
 {
     if (p.segs.size() != 1) return false;
     const Segment& g = p.segs[0];
-    if (!row_group(p.chain, g.cfirst, g.clast) || g.engine != FZ_ENGINE_ROW || g.row_gen) return false;
+    if (!row_group(p.chain, g.cfirst, g.clast) || g.engine != FZ_ENGINE_ROW || g.row_gen || !g.lists) return false;
     for (int i = 0; i < n; ++i)
         if (clips[i].width < 128 || clips[i].height < 8) return false;
     return true;
@@ -35,6 +35,7 @@ static void batch_launch(const fz_plan& p, const fz_clip* clips, int m, BatchLau
 {
     const Segment& g = p.segs[0];
     const bool rgb = g.cfirst == 0, diff = g.clast == 8;
+    const int max_band = row_tallest_band(false, 2, diff, true, p.lds_budget);
     double px = 0.0;
     for (int i = 0; i < m; ++i) px += (double)clips[i].width * clips[i].height * clips[i].frames;
     BatchParams& bp = l.bp;
@@ -58,7 +59,7 @@ static void batch_launch(const fz_plan& p, const fz_clip* clips, int m, BatchLau
         r.nstrips = row_strips(c.width, 2);
         r.strip_step = 128 - 2 * ROW_HX;
         const RowShape s = row_shape(c.height, c.frames, r.nstrips, diff, 0, std::min(BATCH_TT, c.frames),
-                                     std::max(1, (int)(row_slots(2, rgb) * share)), false);
+                                     std::max(1, (int)(row_slots(2, rgb) * share)), false, max_band);
         r.band_h = s.band_h;
         r.tt = s.tt;
         r.nbands = (c.height + r.band_h - 1) / r.band_h;

@@ -297,6 +297,37 @@ __device__ __forceinline__ void list_room(PointList<K>& l, int& held, int dt)
     }
 }
 
+// The same calls for launches whose LDS budget does not hold the lists: each
+// group of points of a row is appended by itself, with no LDS.
+struct PointDirect {
+    const SegParams* p;
+    int x0, t0, dt;  // first column, first frame of the item, frames since
+};
+template <int K>
+__device__ __forceinline__ void list_begin(PointDirect& l, const SegParams& p, int x0, int t0)
+{
+    l = PointDirect{&p, x0, t0, 0};
+}
+template <int K>
+__device__ __forceinline__ void list_put(PointDirect& l, int&, unsigned long long, uint32_t bits, uint32_t row,
+                                         uint32_t lane_tag, const float (&r)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        emit_points(*l.p, (bits >> k & 1u) != 0u, (uint32_t)(l.t0 + l.dt), row,
+                    (uint32_t)(l.x0 + K * (int)(lane_tag & 63u) + k), r[k]);
+}
+template <int K, class F>
+__device__ __forceinline__ void march_points(PointDirect&, int& held, F&& march)
+{
+    march(held, false);
+}
+template <int K>
+__device__ __forceinline__ void list_room(PointDirect& l, int&, int dt)
+{
+    l.dt = dt;
+}
+
 // Start of a workgroup (every wavefront, before any leaves).
 template <int K, int WAVES>
 __device__ __forceinline__ void lists_begin(PointLists<K, WAVES>& l)

@@ -26,6 +26,7 @@ struct Segment {
     int engine;             // FZ_ENGINE_TILE / ROW / STREAM
     int row_k, nstrips, nbands, nchunks;  // row-marching geometry
     int row_gen;            // 1: generic row kernel, 0: the Harris-chain kernel
+    int lists;              // row kernels: feature points are collected in LDS
     double bytes_per_px;
     double cost;
     int refused;            // a request this group's kernel cannot run (cost is +inf): 1 a band, 2 an IIR frame run

@@ -85,21 +85,39 @@ Segment price_group(const fz_plan& p, int a, int b, int req_w, int req_h, int re
         s.engine = FZ_ENGINE_ROW;
         s.row_gen = row_generic ? 1 : 0;
         const bool diff = chain_op(ch, B) == FZ_OP_FRAMEDIFF;
-        s.row_k = row_generic ? 2 : row_strips_best(p.W, rgb_in);
-        s.nstrips = row_strips(p.W, s.row_k, row_generic ? s.halo : ROW_HX);
-        const int slots = row_generic ? ROW_SLOTS_GENERIC : row_slots(s.row_k, rgb_in);
-        const RowShape rs = row_shape(p.H, p.T, s.nstrips, diff, req_h, req_tpb, slots, row_generic);
-        if (rs.band_h == 0) {
+        bool nms = false;
+        for (int j = A; j <= B; ++j) nms |= chain_op(ch, j) == FZ_OP_NMS3;
+        if (diff && std::min(req_h, p.H) > ROW_DIFF_MAX_BAND) {
             s.refused = 1;
             return s;
         }
+        // The first form whose bands the budget holds (16 rows, or the requested
+        // ones): points collected in LDS or appended as they are found, each with two
+        // columns a lane where three are the choice but take more LDS.
+        const int K = row_generic ? 2 : row_strips_best(p.W, rgb_in);
+        const int need = req_h > 0 ? std::min(req_h, p.H) : diff ? std::min(16, p.H) : 1;
+        auto shape = [&](int k, bool generic, int band_req, int max_band) {
+            s.nstrips = row_strips(p.W, k, row_generic ? s.halo : ROW_HX);
+            return row_shape(p.H, p.T, s.nstrips, diff, band_req, req_tpb,
+                             row_generic ? ROW_SLOTS_GENERIC : row_slots(k, rgb_in), generic, max_band);
+        };
+        // Which budgets admit a group does not move with the fitted sizing: those that
+        // hold the mask bytes of the band the general model takes.
+        if (req_h <= 0 && diff && row_lds_bytes(shape(K, true, 0, ROW_DIFF_MAX_BAND).band_h) > p.lds_budget) return s;
+        RowShape rs{};
+        for (int form = nms ? 0 : 2; form < 4 && rs.band_h == 0; ++form) {
+            s.lists = form < 2;
+            s.row_k = form % 2 == 0 ? K : 2;
+            const int max_band = row_tallest_band(row_generic, s.row_k, diff, s.lists != 0, p.lds_budget);
+            if (max_band >= need) rs = shape(s.row_k, row_generic, req_h, max_band);
+        }
+        if (rs.band_h == 0) return s;
         s.tpb = rs.tt;
         s.nchunks = (p.T + s.tpb - 1) / s.tpb;
         s.tile_h = rs.band_h;
         s.nbands = (p.H + s.tile_h - 1) / s.tile_h;
         s.tile_w = 64 * s.row_k;
         s.lds_bytes = diff ? row_lds_bytes(s.tile_h) : 0;
-        if (s.lds_bytes > p.lds_budget) return s;
         s.tile = 0;
     } else {
         s.engine = FZ_ENGINE_TILE;

@@ -32,6 +32,8 @@
 // The input rows are prefetched two iterations ahead.
 #pragma once
 
+#include <type_traits>
+
 #include "engine.h"
 #include "rowgeom.h"
 
@@ -248,9 +250,9 @@ __device__ __forceinline__ void load_raw(const RowCtx& c, int row, RawRow<RowSta
 // 255 where bit `i` of w is set, else 0.
 __device__ __forceinline__ uint8_t byte_mask(uint32_t w, int i) { return (uint8_t)((int32_t)(w << (31 - i)) >> 31); }
 
-template <int K, bool RGB, bool DIFF, bool EL, bool ER, int U>
-__device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, PointList<K>& list,
-                                         int& ev, int j)
+template <int K, bool RGB, bool DIFF, bool EL, bool ER, int U, class L>
+__device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, L& list, int& ev,
+                                         int j)
 {
     constexpr int U3 = U % 3, U5 = U % 5;
     const int row_in = c.y0 - ROW_HX + j;
@@ -403,10 +405,9 @@ __device__ __forceinline__ void row_step(RowState<K, RGB>& st, const RowCtx& c, 
     }
 }
 
-template <int K, bool RGB, bool DIFF, bool EL, bool ER, int... U>
-__device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p,
-                                          PointList<K>& list, int& ev, int jb, int n,
-                                          std::integer_sequence<int, U...>)
+template <int K, bool RGB, bool DIFF, bool EL, bool ER, class L, int... U>
+__device__ __forceinline__ void row_block(RowState<K, RGB>& st, const RowCtx& c, const SegParams& p, L& list, int& ev,
+                                          int jb, int n, std::integer_sequence<int, U...>)
 {
     ((jb + U < n ? row_step<K, RGB, DIFF, EL, ER, U>(st, c, p, list, ev, jb + U) : void()), ...);
 }
@@ -507,9 +508,8 @@ __device__ __forceinline__ RowBoundary row_boundary(RowGeomK& rp, int strip, int
 }
 
 // All frames of one work item.
-template <int K, bool RGB, bool DIFF, bool EL, bool ER>
-__device__ __forceinline__ void row_frames(RowCtx& c, const SegParams& p, bool exchange, int geom_at,
-                                           PointList<K>& list, int& held, int strip, int band, int ts, int t0, int t1)
+template <int K, bool RGB, bool DIFF, bool EL, bool ER, class L>
+__device__ __forceinline__ void row_frames(RowCtx& c, const SegParams& p, bool exchange, int geom_at, L& list, int& held, int strip, int band, int ts, int t0, int t1)
 {
     constexpr int C = RGB ? 3 : 1;
     const size_t plane = (size_t)p.W * p.H;
@@ -566,9 +566,9 @@ struct RowItem {
 // One work item of one wavefront (all of it wavefront-uniform).  geom_at: the
 // byte of its RowGeom in the kernel arguments; exchange: whether that has
 // exchange buffers.  Returns the entries left in its point list.
-template <int K, bool RGB, bool DIFF>
+template <int K, bool RGB, bool DIFF, class L>
 __device__ __forceinline__ int row_item(const SegParams& p, const RowItem& it, bool exchange, int geom_at,
-                                        uint8_t* prev_lds, PointList<K>& list)
+                                        uint8_t* prev_lds, L& list)
 {
     RowCtx c;
     c.W = p.W;
@@ -628,7 +628,9 @@ __device__ __forceinline__ int row_item(const SegParams& p, const RowItem& it, b
     list_begin<K>(list, p, c.x0, t0);
     int held = 0;
     const bool el = it.strip == 0, er = it.strip == it.nstrips - 1;
-    if (el && er)
+    if constexpr (std::is_same_v<L, PointDirect>)
+        row_frames<K, RGB, DIFF, true, true>(c, p, exchange, geom_at, list, held, it.strip, it.band, ts, t0, t1);
+    else if (el && er)
         row_frames<K, RGB, DIFF, true, true>(c, p, exchange, geom_at, list, held, it.strip, it.band, ts, t0, t1);
     else if (el)
         row_frames<K, RGB, DIFF, true, false>(c, p, exchange, geom_at, list, held, it.strip, it.band, ts, t0, t1);
@@ -665,6 +667,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64, K == 2 ? (RGB ? 5 : 6) : 4) void k_
 {
     extern __shared__ uint8_t row_lds[];
     __shared__ PointLists<K, ROW_WAVES> lists;
+    static_assert(sizeof(lists) == row_list_bytes(K), "the planner counts these bytes");
     lists_begin(lists);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront-uniform
     const int item = blockIdx.x * ROW_WAVES + wave;
@@ -675,6 +678,22 @@ __global__ __launch_bounds__(ROW_WAVES * 64, K == 2 ? (RGB ? 5 : 6) : 4) void k_
                                             row_lds + wave * row_mask_bytes(K, rp.g.band_h), lists.wave[wave]);
     if (rp.sp.count != nullptr)
         lists_end(lists, wave, held, min(ROW_WAVES, rp.g.total - (int)blockIdx.x * ROW_WAVES));
+}
+
+// The same for plans whose LDS budget does not hold the lists.  (One form of the
+// row loop for every strip: an interior strip's border values are not used.)
+template <int K, bool RGB, bool DIFF>
+__global__ __launch_bounds__(ROW_WAVES * 64) void k_rowfuse_direct(RowParams rp)
+{
+    extern __shared__ uint8_t row_lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = blockIdx.x * ROW_WAVES + wave;
+    if (item >= rp.g.total) return;
+    const RowItem it =
+        row_decompose(item, rp.g.nstrips, rp.g.nbands, rp.g.nchunks, rp.g.band_h, rp.g.tt, rp.g.strip_step);
+    PointDirect list;
+    (void)row_item<K, RGB, DIFF>(rp.sp, it, rp.g.xcount != nullptr, offsetof(RowParams, g),
+                                 row_lds + wave * row_mask_bytes(K, rp.g.band_h), list);
 }
 
 // ---------------------------------------------------------------- batches
@@ -758,5 +777,43 @@ inline hipError_t allow_row_lds(const void* kernel, size_t mask_rows)
 hipError_t launch_rowfuse_batch(const BatchParams& bp, bool rgb, bool diff, int blocks, hipStream_t s);
 
 hipError_t launch_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipStream_t s);
+hipError_t launch_rowfuse_direct(const RowParams& rp, int K, bool rgb, bool diff, hipStream_t s);
+
+// Zero n words (the frame-boundary arrival counters) and the point count (null:
+// none); a kernel, not a memset, so that it is an ordinary kernel node when a run
+// is captured into a graph.
+hipError_t zero_words(uint32_t* p, int n, uint32_t* count, hipStream_t s);
+
+template <bool LISTS, int K, bool RGB, bool DIFF>
+hipError_t launch_rowfuse_t(const RowParams& rp, hipStream_t s)
+{
+    const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
+    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.g.band_h) : 0;
+    const int nb = DIFF && rp.g.xcount != nullptr ? row_boundaries(rp.g.nstrips, rp.g.nbands, rp.g.nchunks) : 0;
+    hipError_t e = nb > 0 || rp.sp.count != nullptr ? zero_words(rp.g.xcount, nb, rp.sp.count, s) : hipSuccess;
+    if (e != hipSuccess) return e;
+    auto go = [&](auto kern) {
+        if ((e = allow_row_lds((const void*)kern, lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
+        return hipGetLastError();
+    };
+    if constexpr (LISTS)
+        return go(k_rowfuse<K, RGB, DIFF>);
+    else
+        return go(k_rowfuse_direct<K, RGB, DIFF>);
+}
+template <bool LISTS>
+hipError_t pick_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipStream_t s)
+{
+    if (K == 2) {
+        if (rgb) return diff ? launch_rowfuse_t<LISTS, 2, true, true>(rp, s) : launch_rowfuse_t<LISTS, 2, true, false>(rp, s);
+        return diff ? launch_rowfuse_t<LISTS, 2, false, true>(rp, s) : launch_rowfuse_t<LISTS, 2, false, false>(rp, s);
+    }
+    if (K == 3) {
+        if (rgb) return diff ? launch_rowfuse_t<LISTS, 3, true, true>(rp, s) : launch_rowfuse_t<LISTS, 3, true, false>(rp, s);
+        return diff ? launch_rowfuse_t<LISTS, 3, false, true>(rp, s) : launch_rowfuse_t<LISTS, 3, false, false>(rp, s);
+    }
+    return hipErrorInvalidValue;
+}
 
 }  // namespace fz

@@ -12,45 +12,21 @@ __global__ void k_batch_reset(BatchParams bp)
     if (i < bp.n_clips && bp.clip[i].count != nullptr) *bp.clip[i].count = 0u;
 }
 
-// Zero n words (the frame-boundary arrival counters) and the point count (null:
-// none); a kernel, not a memset, so that it is an ordinary kernel node when a run
-// is captured into a graph.
 __global__ void k_zero_words(uint32_t* p, int n, uint32_t* count)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
     if (i == 0 && count != nullptr) *count = 0u;
 }
-
-template <int K, bool RGB, bool DIFF>
-static hipError_t go(const RowParams& rp, hipStream_t s)
+hipError_t zero_words(uint32_t* p, int n, uint32_t* count, hipStream_t s)
 {
-    const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
-    const size_t lds = DIFF ? (size_t)ROW_WAVES * row_mask_bytes(K, rp.g.band_h) : 0;
-    const int nb = DIFF && rp.g.xcount != nullptr ? row_boundaries(rp.g.nstrips, rp.g.nbands, rp.g.nchunks) : 0;
-    if (nb > 0 || rp.sp.count != nullptr) {
-        hipLaunchKernelGGL(k_zero_words, dim3(std::max(1, (nb + 255) / 256)), dim3(256), 0, s, rp.g.xcount, nb,
-                           rp.sp.count);
-        const hipError_t z = hipGetLastError();
-        if (z != hipSuccess) return z;
-    }
-    const hipError_t e = allow_row_lds((const void*)k_rowfuse<K, RGB, DIFF>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rowfuse<K, RGB, DIFF>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
+    hipLaunchKernelGGL(k_zero_words, dim3(std::max(1, (n + 255) / 256)), dim3(256), 0, s, p, n, count);
     return hipGetLastError();
 }
 
 hipError_t launch_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipStream_t s)
 {
-    if (K == 2) {
-        if (rgb) return diff ? go<2, true, true>(rp, s) : go<2, true, false>(rp, s);
-        return diff ? go<2, false, true>(rp, s) : go<2, false, false>(rp, s);
-    }
-    if (K == 3) {
-        if (rgb) return diff ? go<3, true, true>(rp, s) : go<3, true, false>(rp, s);
-        return diff ? go<3, false, true>(rp, s) : go<3, false, false>(rp, s);
-    }
-    return hipErrorInvalidValue;
+    return pick_rowfuse<true>(rp, K, rgb, diff, s);
 }
 
 template <bool RGB, bool DIFF>

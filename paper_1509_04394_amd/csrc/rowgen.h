@@ -84,7 +84,11 @@ struct GenCtx {
     int lane_in;        // element offset of this lane's first column in an input row
     uint8_t* prev;
     uint32_t tag;       // frame t's number in the item << 16 (feature points)
-    PointList<2>* list;  // this wavefront's points (LDS; groups with the suppression stage)
+};
+// With this wavefront's points (groups with the suppression stage): PointList<K> or PointDirect.
+template <class L>
+struct GenListCtx : GenCtx {
+    L* list;
     int* ev;            // entries found
 };
 
@@ -199,13 +203,13 @@ __device__ __forceinline__ void gen_store(const GenCtx& c, int row, const float 
     }
 }
 
-template <int CH, int A, int B, int K, bool EDGE, int S, int U>
-__device__ __forceinline__ void gen_window(GenState<CH, A, B, K>& st, const GenCtx& c, const SegParams& p, int r_in,
+template <int CH, int A, int B, int K, bool EDGE, int S, int U, class C>
+__device__ __forceinline__ void gen_window(GenState<CH, A, B, K>& st, const C& c, const SegParams& p, int r_in,
                                            bool have, float (&v)[3][K]);
 
 // Window stages from S on (S > last window: the final row, stored).
-template <int CH, int A, int B, int K, bool EDGE, int S, int U>
-__device__ __forceinline__ void gen_from(GenState<CH, A, B, K>& st, const GenCtx& c, const SegParams& p, int r_in,
+template <int CH, int A, int B, int K, bool EDGE, int S, int U, class C>
+__device__ __forceinline__ void gen_from(GenState<CH, A, B, K>& st, const C& c, const SegParams& p, int r_in,
                                          bool have, float (&v)[3][K])
 {
     using I = GenInfo<CH, A, B>;
@@ -235,8 +239,8 @@ __device__ __forceinline__ void gen_from(GenState<CH, A, B, K>& st, const GenCtx
     }
 }
 
-template <int CH, int A, int B, int K, bool EDGE, int S, int U>
-__device__ __forceinline__ void gen_window(GenState<CH, A, B, K>& st, const GenCtx& c, const SegParams& p, int r_in,
+template <int CH, int A, int B, int K, bool EDGE, int S, int U, class C>
+__device__ __forceinline__ void gen_window(GenState<CH, A, B, K>& st, const C& c, const SegParams& p, int r_in,
                                            bool have, float (&v)[3][K])
 {
     using I = GenInfo<CH, A, B>;
@@ -369,8 +373,8 @@ __device__ __forceinline__ void gen_window(GenState<CH, A, B, K>& st, const GenC
     }
 }
 
-template <int CH, int A, int B, int K, bool EDGE, int U>
-__device__ __forceinline__ void gen_step(GenState<CH, A, B, K>& st, const GenCtx& c, const SegParams& p, int j)
+template <int CH, int A, int B, int K, bool EDGE, int U, class C>
+__device__ __forceinline__ void gen_step(GenState<CH, A, B, K>& st, const C& c, const SegParams& p, int j)
 {
     using I = GenInfo<CH, A, B>;
     const int row_in = c.y0 - I::H + j;
@@ -383,15 +387,15 @@ __device__ __forceinline__ void gen_step(GenState<CH, A, B, K>& st, const GenCtx
     gen_from<CH, A, B, K, EDGE, I::W0, U>(st, c, p, row_in, have, v);
 }
 
-template <int CH, int A, int B, int K, bool EDGE, int... U>
-__device__ __forceinline__ void gen_block(GenState<CH, A, B, K>& st, const GenCtx& c, const SegParams& p, int jb,
+template <int CH, int A, int B, int K, bool EDGE, class C, int... U>
+__device__ __forceinline__ void gen_block(GenState<CH, A, B, K>& st, const C& c, const SegParams& p, int jb,
                                           int n, std::integer_sequence<int, U...>)
 {
     ((jb + U < n ? gen_step<CH, A, B, K, EDGE, U>(st, c, p, jb + U) : void()), ...);
 }
 
-template <int CH, int A, int B, int K, bool EDGE>
-__device__ __forceinline__ void gen_frames(GenCtx& c, const SegParams& p, int& held, int ts, int t0, int t1)
+template <int CH, int A, int B, int K, bool EDGE, class C>
+__device__ __forceinline__ void gen_frames(C& c, const SegParams& p, int& held, int ts, int t0, int t1)
 {
     using I = GenInfo<CH, A, B>;
     const int n = c.y1 - c.y0 + 2 * I::H;
@@ -419,11 +423,11 @@ __device__ __forceinline__ void gen_frames(GenCtx& c, const SegParams& p, int& h
     }
 }
 
-template <int CH, int A, int B, int K>
-__device__ __forceinline__ int gen_item(const SegParams& p, const RowItem& it, uint8_t* prev_lds, PointList<K>* list)
+template <int CH, int A, int B, int K, class L>
+__device__ __forceinline__ int gen_item(const SegParams& p, const RowItem& it, uint8_t* prev_lds, L* list)
 {
     using I = GenInfo<CH, A, B>;
-    GenCtx c;
+    GenListCtx<L> c;
     c.in = p.in;
     c.out = p.out;
     c.W = p.W;
@@ -459,16 +463,15 @@ __device__ __forceinline__ int gen_item(const SegParams& p, const RowItem& it, u
     return held;
 }
 
-template <int CH, int A, int B, int K>
+template <int CH, int A, int B, int K, bool LISTS>
 __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowgen(RowParams rp)
 {
-    using I = GenInfo<CH, A, B>;
     extern __shared__ uint8_t gen_lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int item = blockIdx.x * ROW_WAVES + wave;
     const RowItem it = row_decompose(item, rp.g.nstrips, rp.g.nbands, rp.g.nchunks, rp.g.band_h, rp.g.tt, rp.g.strip_step);
     uint8_t* prev = gen_lds + wave * rp.g.band_h * 64;
-    if constexpr (I::HAS_NMS) {
+    if constexpr (LISTS) {
         __shared__ PointLists<K, ROW_WAVES> lists;
         lists_begin(lists);
         if (item >= rp.g.total) return;
@@ -477,25 +480,32 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void k_rowgen(RowParams rp)
             lists_end(lists, wave, held, min(ROW_WAVES, rp.g.total - (int)blockIdx.x * ROW_WAVES));
     } else {
         if (item >= rp.g.total) return;
-        (void)gen_item<CH, A, B, K>(rp.sp, it, prev, nullptr);
+        PointDirect direct;
+        (void)gen_item<CH, A, B, K>(rp.sp, it, prev, &direct);
     }
 }
 
+// lists: collect feature points in LDS (groups with the suppression stage only).
 template <int CH, int A, int B, int K>
-hipError_t launch_rowgen_t(const RowParams& rp, hipStream_t s)
+hipError_t launch_rowgen_t(const RowParams& rp, bool lists, hipStream_t s)
 {
-    if constexpr (A > B || B >= chain_len(CH) || !group_has_window(CH, A, B)) {
+    if constexpr (A > B || B >= chain_len(CH) || !group_has_window(CH, A, B) || row_group(CH, A, B)) {
         return hipErrorInvalidValue;
     } else {
         const int blocks = (rp.g.total + ROW_WAVES - 1) / ROW_WAVES;
         const size_t lds = GenInfo<CH, A, B>::DIFF ? (size_t)ROW_WAVES * rp.g.band_h * 64 : 0;
-        const hipError_t e = allow_row_lds((const void*)k_rowgen<CH, A, B, K>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_rowgen<CH, A, B, K>), dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
-        return hipGetLastError();
+        auto go = [&](auto kern) {
+            const hipError_t e = allow_row_lds((const void*)kern, lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(ROW_WAVES * 64), lds, s, rp);
+            return hipGetLastError();
+        };
+        if constexpr (GenInfo<CH, A, B>::HAS_NMS)
+            if (lists) return go(k_rowgen<CH, A, B, K, true>);
+        return go(k_rowgen<CH, A, B, K, false>);
     }
 }
 
-using RowGenFn = hipError_t (*)(const RowParams&, hipStream_t);
+using RowGenFn = hipError_t (*)(const RowParams&, bool, hipStream_t);
 
 }  // namespace fz

@@ -22,7 +22,7 @@ constexpr int ROW_SLOTS_GENERIC = 256 * 4 * 4;
 
 // Groups the row kernel implements: gray conversion or Gaussian first, suppression
 // or frame difference last, of the Harris chain.
-inline bool row_group(int ch, int A, int B) { return ch == CHAIN_HARRIS && (A == 0 || A == 1) && (B == 7 || B == 8); }
+constexpr bool row_group(int ch, int A, int B) { return ch == CHAIN_HARRIS && (A == 0 || A == 1) && (B == 7 || B == 8); }
 
 // Strips of 64*K columns that overlap by 2*halo cover a frame of width W.
 inline int row_strips(int W, int K, int halo = ROW_HX)
@@ -59,9 +59,31 @@ constexpr int row_mask_bytes(int K, int band_h)
     return row_mask_groups(K, band_h) * row_mask_rows(K) * row_mask_pitch(K);
 }
 // The on-chip memory a plan states for a frame-difference row group: a byte a
-// lane and row, which the generic row kernel takes and the packed words of the
-// Harris kernel stay below from 5 rows on.
+// lane and row.  What the kernels hold is row_held_bytes; a plan's budget has to
+// cover both.
 inline int row_lds_bytes(int band_h) { return ROW_WAVES * band_h * 64; }
+// The feature-point lists of a workgroup (PointLists, groups with the suppression stage).
+constexpr int row_list_bytes(int K) { return ROW_WAVES * (256 * (2 + K) + 32) + 8; }
+// LDS of a row group's workgroup: the previous frame's mask of a frame-difference
+// group (bytes in the generic kernel, packed words in the Harris kernel), and the
+// point lists where the points are collected.
+constexpr int row_held_bytes(bool generic, int K, int band_h, bool diff, bool lists)
+{
+    return (diff ? ROW_WAVES * (generic ? 64 * band_h : row_mask_bytes(K, band_h)) : 0) + (lists ? row_list_bytes(K) : 0);
+}
+
+// A frame-difference group's bands have at most this many rows: one byte of
+// previous-frame mask bits per lane and band row in LDS (64 * band_h per
+// wavefront) is then at most 64 KB for a workgroup of ROW_WAVES wavefronts.
+constexpr int ROW_DIFF_MAX_BAND = 256;
+// The tallest band within `budget` bytes of LDS, stated and held (0: none).
+inline int row_tallest_band(bool generic, int K, bool diff, bool lists, int budget)
+{
+    if (!diff) return row_held_bytes(generic, K, 0, false, lists) <= budget ? 1 << 30 : 0;
+    int b = ROW_DIFF_MAX_BAND;
+    while (b > 0 && std::max(row_lds_bytes(b), row_held_bytes(generic, K, b, true, lists)) > budget) --b;
+    return b;
+}
 
 // Frame boundaries between consecutive runs of one strip and band, and the
 // device bytes of their exchange (two areas of a word a lane and mask group and
@@ -75,11 +97,6 @@ inline size_t row_exchange_bytes(int nstrips, int nbands, int nchunks, int band_
     const size_t nb = (size_t)row_boundaries(nstrips, nbands, nchunks);
     return nb == 0 ? 0 : 2 * nb * row_mask_groups(K, band_h) * 256 + ((nb * 4 + 255) & ~(size_t)255);
 }
-
-// A frame-difference group keeps one byte of previous-frame mask bits per lane
-// and row in LDS: at most 256 rows per band keep that within 64 KB per
-// workgroup of ROW_WAVES wavefronts.
-constexpr int ROW_DIFF_MAX_BAND = 256;
 
 // Rows per band and frames per work item, from a model of the launch's time.
 //
@@ -113,7 +130,9 @@ constexpr int ROW_DIFF_MAX_BAND = 256;
 // are kept as given, except that a frame run longer than the video is the
 // whole video and a band taller than the frame the whole frame; a request the
 // kernel cannot run (a band over ROW_DIFF_MAX_BAND rows on a frame-difference
-// group) gives band_h = 0 and is refused by the caller, never replaced.
+// group) gives band_h = 0 and is refused by the caller, never replaced.  Bands
+// of the planner's choice have at most max_band rows (LDS); where none can, band_h
+// is 0 too.
 struct RowShape {
     int band_h, tt;
 };
@@ -123,9 +142,10 @@ inline double row_time(int bh, double frames, double items, int slots)
     const double r = items / (double)slots, w = (bh + 8.9) * frames + 9.7;
     return w * (r + 0.083 * (std::ceil(r) - r) + 0.9);
 }
-inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic)
+inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic, int max_band)
 {
     if (req_h > 0 && diff && std::min(req_h, H) > ROW_DIFF_MAX_BAND) return RowShape{0, 0};
+    if (req_h <= 0 && max_band < 1) return RowShape{0, 0};
     if (generic && !diff && req_h <= 0) {
         auto even = [&](int rows) {
             const int nb = std::max(1, (H + rows / 2) / rows);
@@ -155,7 +175,7 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
         }
         for (int nb = 1; nb <= H; ++nb) {
             const int bh = req_h > 0 ? std::min(req_h, H) : (H + nb - 1) / nb;
-            if (diff && bh > ROW_DIFF_MAX_BAND) continue;
+            if (req_h <= 0 && bh > max_band) continue;
             if (bh < least && req_h <= 0 && nb > 1) break;
             const long long items = (long long)nstrips * ((H + bh - 1) / bh) * ((T + t - 1) / t);
             const double xch = diff && t < T ? 1.0 : 0.0;

@@ -116,7 +116,7 @@ fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_
                 rp.g.strip_step = 64 * g.row_k - 2 * g.halo;
                 RowGenFn fn = lookup_rowgen(p.chain, g.cfirst, g.clast);
                 if (!fn) return fail(FZ_E_UNSUPPORTED, "no row kernel compiled for this group");
-                e = fn(rp, s);
+                e = fn(rp, g.lists != 0, s);
             } else {
                 rp.g.strip_step = 64 * g.row_k - 2 * ROW_HX;
                 if (exchange_bytes(p, g) > 0) {
@@ -132,7 +132,7 @@ fz_status run_plan(const fz_plan& p, const void* d_in, void* d_out, fz_point* d_
                         rp.g.xcount = (uint32_t*)(xch + 2 * nb * row_mask_groups(g.row_k, g.tile_h) * 256);
                     }
                 }
-                e = launch_rowfuse(rp, g.row_k, g.cfirst == 0, g.clast == 8, s);
+                e = (g.lists ? launch_rowfuse : launch_rowfuse_direct)(rp, g.row_k, g.cfirst == 0, g.clast == 8, s);
             }
         } else {
             LaunchFn fn = lookup(p.chain, g.cfirst, g.clast);
