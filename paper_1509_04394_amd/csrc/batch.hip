@@ -59,7 +59,7 @@ static void batch_launch(const fz_plan& p, const fz_clip* clips, int m, BatchLau
         r.nstrips = row_strips(c.width, 2);
         r.strip_step = 128 - 2 * ROW_HX;
         const RowShape s = row_shape(c.height, c.frames, r.nstrips, diff, 0, std::min(BATCH_TT, c.frames),
-                                     std::max(1, (int)(row_slots(2, rgb) * share)), false, max_band);
+                                     std::max(1, (int)(row_slots(2, rgb) * share)), false, max_band, 2);
         r.band_h = s.band_h;
         r.tt = s.tt;
         r.nbands = (c.height + r.band_h - 1) / r.band_h;

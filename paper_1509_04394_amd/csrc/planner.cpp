@@ -99,7 +99,7 @@ Segment price_group(const fz_plan& p, int a, int b, int req_w, int req_h, int re
         auto shape = [&](int k, bool generic, int band_req, int max_band) {
             s.nstrips = row_strips(p.W, k, row_generic ? s.halo : ROW_HX);
             return row_shape(p.H, p.T, s.nstrips, diff, band_req, req_tpb,
-                             row_generic ? ROW_SLOTS_GENERIC : row_slots(k, rgb_in), generic, max_band);
+                             row_generic ? ROW_SLOTS_GENERIC : row_slots(k, rgb_in), generic, max_band, k);
         };
         // Which budgets admit a group does not move with the fitted sizing: those that
         // hold the mask bytes of the band the general model takes.

@@ -76,6 +76,13 @@ constexpr int row_held_bytes(bool generic, int K, int band_h, bool diff, bool li
 // previous-frame mask bits per lane and band row in LDS (64 * band_h per
 // wavefront) is then at most 64 KB for a workgroup of ROW_WAVES wavefronts.
 constexpr int ROW_DIFF_MAX_BAND = 256;
+// Wavefronts at once of the Harris row kernel: `slots` as its registers allow, or
+// those of the workgroups the LDS holds (three columns a lane, bands over 170
+// rows: 365x800x10000 RGB at 200 rows 6.47 ms, at 160 5.58).
+inline int row_resident(int slots, int K, int band_h, bool diff)
+{
+    return std::min(slots, 256 * ROW_WAVES * (163840 / row_held_bytes(false, K, band_h, diff, true)));
+}
 // The tallest band within `budget` bytes of LDS, stated and held (0: none).
 inline int row_tallest_band(bool generic, int K, bool diff, bool lists, int budget)
 {
@@ -142,7 +149,8 @@ inline double row_time(int bh, double frames, double items, int slots)
     const double r = items / (double)slots, w = (bh + 8.9) * frames + 9.7;
     return w * (r + 0.083 * (std::ceil(r) - r) + 0.9);
 }
-inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic, int max_band)
+inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int req_tt, int slots, bool generic, int max_band,
+                          int K)
 {
     if (req_h > 0 && diff && std::min(req_h, H) > ROW_DIFF_MAX_BAND) return RowShape{0, 0};
     if (req_h <= 0 && max_band < 1) return RowShape{0, 0};
@@ -187,7 +195,7 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
                 const double r = (double)items / (double)fit;
                 cost = (double)items * (bh + 2 * ROW_HX) * (t + 0.45 * xch) * (1.0 + 1.0 / r) * ((double)slots / (double)fit);
             } else {
-                cost = row_time(bh, t + 0.15 * xch, (double)items, slots);
+                cost = row_time(bh, t + 0.15 * xch, (double)items, row_resident(slots, K, bh, diff));
             }
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
@@ -217,7 +225,8 @@ inline RowRun row_run(size_t room, int T, int nstrips, int nbands, int band_h, i
     for (int t = tt;; t = t > T / 2 ? T : 2 * t) {
         const int n = (T + t - 1) / t;
         const bool fits = row_exchange_bytes(nstrips, nbands, n, band_h, K) <= room;
-        const double time = row_time(band_h, t + (n == 1 ? 0.0 : fits ? 0.15 : 1.0), (double)nstrips * nbands * n, slots);
+        const double time = row_time(band_h, t + (n == 1 ? 0.0 : fits ? 0.15 : 1.0), (double)nstrips * nbands * n,
+                                     row_resident(slots, K, band_h, true));
         if (best_time < 0.0 || time < best_time) {
             best = RowRun{t, n, fits && n > 1};
             best_time = time;

@@ -94,3 +94,13 @@ def test_header_counts_the_same_bytes(tmp_path):
     out = hostcpp.run(tmp_path, ["rowgeom.h"], "".join(
         f'printf("%d\\n", row_held_bytes(false, {k}, {b}, true, {l}));' for k, b, l in cases))
     assert [int(v) for v in out] == [masks(k, b) + (lists(k) if l else 0) for k, b, l in cases]
+
+
+@pytest.mark.parametrize("W,H,T", [(365, 800, 10000), (729, 600, 10000), (192, 600, 20000), (365, 1000, 4000)])
+@pytest.mark.parametrize("ops", [RGB, GRAY], ids=["rgb", "gray"])
+def test_tall_bands_leave_room_for_the_wavefronts(ops, W, H, T):
+    # four wavefronts a SIMD with three columns a lane, as the registers allow: the
+    # sizing counts them, so four workgroups must fit a compute unit
+    s = planned(ops, W, H, T, 0)
+    k = s.tile_w // 64
+    assert (4 if k == 3 else 6 if ops is GRAY else 5) * (masks(k, s.tile_h) + lists(k)) <= 163840
