@@ -182,11 +182,16 @@ fz_status run_batch(fz_plan& p, const fz_clip* clips, int n, void* ws, size_t ws
     hipStream_t user = (hipStream_t)stream;
     (void)hipGetLastError();  // drop an error latched by earlier, unrelated runtime calls
     std::vector<uint64_t> key = batch_key(clips, n, ws, ws_bytes);
+    // (a batch that is captured was checked when it was)
     if (p.batch_exec && key == p.batch_key) {
         hipError_t e = hipGraphLaunch((hipGraphExec_t)p.batch_exec, user);
         if (e != hipSuccess) return fail(FZ_E_HIP, std::string("batch graph launch: ") + hipGetErrorString(e));
         return FZ_OK;
     }
+    const size_t need = batch_workspace_bytes(p, clips, n);
+    if (need == (size_t)-1) return fail(FZ_E_LDS, "fz_run_batch: the partition does not fit some clip's size");
+    if (need > 0 && (!ws || ws_bytes < need))
+        return fail(FZ_E_WORKSPACE, "fz_run_batch: workspace needs " + std::to_string(need) + " bytes");
     release_graph(p);
     hipError_t e = hipSuccess;
     if (!p.capture_stream) {

@@ -858,10 +858,6 @@ fz_status fz_run_batch(fz_plan* plan, const fz_clip* clips, int32_t n_clips, voi
         if ((int64_t)c.width * c.height > (int64_t)1 << 28) return fail(FZ_E_INVALID, where + "frame too large");
         if (c.point_capacity > 0 && !c.d_points) return fail(FZ_E_INVALID, where + "capacity without a point buffer");
     }
-    const size_t need = batch_workspace_bytes(*plan, clips, n_clips);
-    if (need == (size_t)-1) return fail(FZ_E_LDS, "fz_run_batch: the partition does not fit some clip's size");
-    if (need > 0 && (!d_workspace || ws_bytes < need))
-        return fail(FZ_E_WORKSPACE, "fz_run_batch: workspace needs " + std::to_string(need) + " bytes");
     return run_batch(*plan, clips, n_clips, d_workspace, ws_bytes, stream);
 }
 

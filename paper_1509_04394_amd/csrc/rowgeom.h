@@ -181,9 +181,10 @@ inline RowShape row_shape(int H, int T, int nstrips, bool diff, int req_h, int r
         } else if ((!diff && t != 1) || (t > T && t != 1)) {
             continue;
         }
-        for (int nb = 1; nb <= H; ++nb) {
+        for (int nb = 1, last = 0; nb <= H; ++nb) {
             const int bh = req_h > 0 ? std::min(req_h, H) : (H + nb - 1) / nb;
-            if (req_h <= 0 && bh > max_band) continue;
+            if (bh == last || (req_h <= 0 && bh > max_band)) continue;
+            last = bh;
             if (bh < least && req_h <= 0 && nb > 1) break;
             const long long items = (long long)nstrips * ((H + bh - 1) / bh) * ((T + t - 1) / t);
             const double xch = diff && t < T ? 1.0 : 0.0;

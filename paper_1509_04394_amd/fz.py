@@ -684,8 +684,8 @@ def make_clip(x, out, points=None, count=None, width=None, height=None, frames=N
 def run_batch(plan: "Plan", clips, workspace=None, stream=None):
     """Run `plan` over fz_clip descriptors (device buffers owned by the caller)."""
     import torch
-    need = fz_batch_workspace_bytes(plan.handle, clips)
     if workspace is None:
+        need = fz_batch_workspace_bytes(plan.handle, clips)
         workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device="cuda")
     if stream is None:
         stream = torch.cuda.current_stream().cuda_stream
