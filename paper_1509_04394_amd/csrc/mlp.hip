@@ -308,24 +308,11 @@ __global__ void k_mlp_adam(float* __restrict__ prm, const float* __restrict__ gr
     prm[p] -= lr * mh / (__builtin_sqrtf(vh) + eps);
 }
 
-// Workspace of a training step: the workgroups' partial gradients and losses.
-// (860 bytes a sample at 20 features, and one workgroup's worth at least.)
-static size_t mlp_ws(int F, int n)
-{
-    const int nb = (n + 63) / 64;
-    const size_t act = (size_t)n * MLP_H * 2 * sizeof(float);
-    const size_t yb = (size_t)n * sizeof(float);
-    const size_t part = (size_t)nb * mlp_params(F) * sizeof(float) + (size_t)nb * sizeof(float);
-    return ((act + 255) & ~(size_t)255) + ((yb + 255) & ~(size_t)255) + part + 256;
-}
+// Workgroups of a training step: one a tile, two a compute unit at most.
+static int mlp_blocks(int n) { return (int)std::min<int64_t>(((int64_t)n + MLP_ROWS - 1) / MLP_ROWS, MLP_MAX_BLOCKS); }
 
-// Workgroups of a training step: one a tile, as many as the workspace holds.
-static int mlp_blocks(int F, int n)
-{
-    const size_t fit = mlp_ws(F, n) / ((size_t)(mlp_params(F) + 1) * sizeof(float));
-    const size_t tiles = ((size_t)n + MLP_ROWS - 1) / MLP_ROWS;
-    return (int)std::max<size_t>(1, std::min<size_t>({tiles, fit, (size_t)MLP_MAX_BLOCKS}));
-}
+// Workspace of a training step: the workgroups' partial gradients and losses.
+static size_t mlp_ws(int F, int n) { return (size_t)mlp_blocks(n) * (mlp_params(F) + 1) * sizeof(float); }
 
 }  // namespace fz
 
@@ -363,7 +350,7 @@ fz_status fz_mlp_loss_grad(const float* d_params, int32_t n_features, const floa
         return fail(FZ_E_WORKSPACE, "fz_mlp_loss_grad: workspace needs " + std::to_string(mlp_ws(n_features, n)));
     hipStream_t s = (hipStream_t)stream;
     (void)hipGetLastError();  // drop an error latched by earlier, unrelated runtime calls
-    const int nb = mlp_blocks(n_features, n);
+    const int nb = mlp_blocks(n);
     const int P = mlp_params(n_features);
     float* part = (float*)d_ws;
     float* lpart = part + (size_t)nb * P;
