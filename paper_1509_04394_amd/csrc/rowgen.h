@@ -58,6 +58,10 @@ struct GenInfo {
 };
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <int N>
+struct GenRow {
+    float f[N];
+};
 
 template <int CH, int A, int B, int K>
 struct GenState {
@@ -67,11 +71,10 @@ struct GenState {
     float bh[I::has(FZ_OP_BOXSUM5) ? 5 : 1][3][K];
     float nr[I::HAS_NMS ? 3 : 1][K];
     float nm[I::HAS_NMS ? 3 : 1][K];
-    // input rows, two loaded ahead: u8 bytes as loaded, or f32 words
-    struct Raw {
-        RawRow<I::IN_U8 ? K * I::IN_BYTES : 1> b;
-        uint32_t f[I::IN_U8 ? 1 : K * I::IN_PLANES];
-    } raw[3];
+    // input rows, two loaded ahead: u8 bytes as loaded, or f32 values (each kind
+    // alone: beside an unused byte part the values of a one-plane row stayed an
+    // array, which the compiler kept in LDS or scratch)
+    std::conditional_t<I::IN_U8, RawRow<K * I::IN_BYTES>, GenRow<K * I::IN_PLANES>> raw[3];
 };
 
 struct GenCtx {
@@ -110,15 +113,15 @@ __device__ __forceinline__ void gen_load(const GenCtx& c, int row, Raw& raw)
     if constexpr (I::IN_U8) {
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
             (void*)((const uint8_t*)c.in + fbase * I::IN_BYTES), (short)0, (int)(c.plane * I::IN_BYTES), 0x00020000);
-        load_words<K * I::IN_BYTES>(r, c.lane_in * I::IN_BYTES, row * c.W * I::IN_BYTES, raw.b);
+        load_words<K * I::IN_BYTES>(r, c.lane_in * I::IN_BYTES, row * c.W * I::IN_BYTES, raw);
     } else {
 #pragma unroll
         for (int ch = 0; ch < I::IN_PLANES; ++ch) {
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 (void*)((const float*)c.in + ch * c.vol + fbase), (short)0, (int)(c.plane * 4), 0x00020000);
             const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, 4 * c.lane_in, 4 * row * c.W, 0);  // K == 2
-            raw.f[ch * K] = w.x;
-            raw.f[ch * K + 1] = w.y;
+            raw.f[ch * K] = __uint_as_float(w.x);
+            raw.f[ch * K + 1] = __uint_as_float(w.y);
         }
     }
 }
@@ -133,14 +136,14 @@ __device__ __forceinline__ void gen_unpack(const Raw& raw, float (&v)[3][K], con
     for (int k = 0; k < K; ++k) {
         float px[3];
         if constexpr (I::IN_RGB) {
-            px[0] = (float)byte_at<NB>(raw.b, 3 * k);
-            px[1] = (float)byte_at<NB>(raw.b, 3 * k + 1);
-            px[2] = (float)byte_at<NB>(raw.b, 3 * k + 2);
+            px[0] = (float)byte_at<NB>(raw, 3 * k);
+            px[1] = (float)byte_at<NB>(raw, 3 * k + 1);
+            px[2] = (float)byte_at<NB>(raw, 3 * k + 2);
         } else if constexpr (I::IN_U8) {
-            px[0] = (float)byte_at<NB>(raw.b, k);
+            px[0] = (float)byte_at<NB>(raw, k);
         } else {
 #pragma unroll
-            for (int ch = 0; ch < I::IN_PLANES; ++ch) px[ch] = __uint_as_float(raw.f[ch * K + k]);
+            for (int ch = 0; ch < I::IN_PLANES; ++ch) px[ch] = raw.f[ch * K + k];
         }
         point_run<CH, A, pw_end(CH, A, B)>(px, p);
 #pragma unroll
