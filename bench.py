@@ -67,13 +67,15 @@ KERNEL_OPS = dict(MIN_OPS, gauss5=11, boxsum5=18)
 
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE / WRITE_SIZE
 # passes, scaled by the plain-copy calibration (profiles/rowfuse_rgb800_counters.md).
-# Valid only for the kernel sources and the launch geometry (columns per strip,
-# band rows, frames per work item) they were taken with: the key holds both.
+# Valid only for the kernel sources (every file with a part of the kernel: the row
+# loop, the point lists, the mask and exchange layout, the arithmetic) and the
+# launch geometry (columns per strip, band rows, frames per work item) they were
+# taken with: the key holds both.
 COUNTER_TRAFFIC = {
-    ("rgb800", "6704f1a97f600497", (128, 86, 2)): {"fetch_bytes": 1.993e9, "write_bytes": 0.668e9,
+    ("rgb800", "0f14df3a9096708d", (128, 86, 2)): {"fetch_bytes": 1.989e9, "write_bytes": 0.668e9,
                                                    "source": "profiles/rowfuse_rgb800_counters.md"},
 }
-KERNEL_SOURCES = ["rowfuse.h", "stage_math.h"]
+KERNEL_SOURCES = ["rowfuse.h", "engine.h", "rowgeom.h", "stage_math.h"]
 DRIVER_TIMEOUT_S = 600
 
 

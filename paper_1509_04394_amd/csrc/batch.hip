@@ -1,5 +1,6 @@
-// Batches of clips: one row-kernel launch over every clip's work items when the plan is a single group the row kernel implements, otherwise
-// the clips' groups one clip after another; either way captured once into a
+// Batches of clips: one row-kernel launch over every clip's work items when the
+// plan is a single group the row kernel implements, otherwise the clips' groups
+// one clip after another; either way captured once into a
 // HIP graph and replayed while the clip set is unchanged.
 #include <hip/hip_runtime.h>
 

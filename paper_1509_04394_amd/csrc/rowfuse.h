@@ -509,7 +509,8 @@ __device__ __forceinline__ RowBoundary row_boundary(RowGeomK& rp, int strip, int
 
 // All frames of one work item.
 template <int K, bool RGB, bool DIFF, bool EL, bool ER, class L>
-__device__ __forceinline__ void row_frames(RowCtx& c, const SegParams& p, bool exchange, int geom_at, L& list, int& held, int strip, int band, int ts, int t0, int t1)
+__device__ __forceinline__ void row_frames(RowCtx& c, const SegParams& p, bool exchange, int geom_at, L& list, int& held,
+                                           int strip, int band, int ts, int t0, int t1)
 {
     constexpr int C = RGB ? 3 : 1;
     const size_t plane = (size_t)p.W * p.H;
@@ -805,15 +806,12 @@ hipError_t launch_rowfuse_t(const RowParams& rp, hipStream_t s)
 template <bool LISTS>
 hipError_t pick_rowfuse(const RowParams& rp, int K, bool rgb, bool diff, hipStream_t s)
 {
-    if (K == 2) {
-        if (rgb) return diff ? launch_rowfuse_t<LISTS, 2, true, true>(rp, s) : launch_rowfuse_t<LISTS, 2, true, false>(rp, s);
-        return diff ? launch_rowfuse_t<LISTS, 2, false, true>(rp, s) : launch_rowfuse_t<LISTS, 2, false, false>(rp, s);
-    }
-    if (K == 3) {
-        if (rgb) return diff ? launch_rowfuse_t<LISTS, 3, true, true>(rp, s) : launch_rowfuse_t<LISTS, 3, true, false>(rp, s);
-        return diff ? launch_rowfuse_t<LISTS, 3, false, true>(rp, s) : launch_rowfuse_t<LISTS, 3, false, false>(rp, s);
-    }
-    return hipErrorInvalidValue;
+    hipError_t (*fn)(const RowParams&, hipStream_t) = nullptr;
+    if (K == 2 && rgb) fn = diff ? launch_rowfuse_t<LISTS, 2, true, true> : launch_rowfuse_t<LISTS, 2, true, false>;
+    if (K == 2 && !rgb) fn = diff ? launch_rowfuse_t<LISTS, 2, false, true> : launch_rowfuse_t<LISTS, 2, false, false>;
+    if (K == 3 && rgb) fn = diff ? launch_rowfuse_t<LISTS, 3, true, true> : launch_rowfuse_t<LISTS, 3, true, false>;
+    if (K == 3 && !rgb) fn = diff ? launch_rowfuse_t<LISTS, 3, false, true> : launch_rowfuse_t<LISTS, 3, false, false>;
+    return fn ? fn(rp, s) : hipErrorInvalidValue;
 }
 
 }  // namespace fz

@@ -10,10 +10,12 @@ namespace fz {
 
 constexpr int ROW_HX = 6;     // horizontal and vertical halo of the chain: 2 + 1 + 2 + 1
 constexpr int ROW_WAVES = 4;  // independent wavefronts per workgroup
-// Wavefronts per SIMD of the Harris row kernel, as its registers allow (512
-// per lane, allocated in blocks of 8; the kernel's launch bounds ask for these):
-// two columns per lane take 86 registers with RGB input (5 waves) and 80 with
-// gray input (6 waves), three columns <= 123 (4 waves).
+// Wavefronts per SIMD of the Harris row kernel (512 registers per lane, allocated in
+// blocks of 8; the kernel's launch bounds ask for these): two columns per lane
+// take 86 registers with RGB input (5 waves) and 80 with gray input (6 waves; two
+// or three more go to 8-12 bytes of scratch a lane with the frame difference: at 5
+// waves without them 192x432x600 takes 143 us, at 6 with them 136, the 16-clip
+// batch 2.23 and 2.10 ms), three columns <= 123 (4 waves).
 inline int row_waves(int K, bool rgb) { return K == 3 ? 4 : (rgb ? 5 : 6); }
 // Wavefronts the 256 CUs (4 SIMDs each) hold at once; 4 per SIMD is assumed
 // for the generic row kernel.
