@@ -103,7 +103,9 @@ Segment price_group(const fz_plan& p, int a, int b, int req_w, int req_h, int re
         };
         // Which budgets admit a group does not move with the fitted sizing: those that
         // hold the mask bytes of the band the general model takes.
-        if (req_h <= 0 && diff && row_lds_bytes(shape(K, true, 0, ROW_DIFF_MAX_BAND).band_h) > p.lds_budget) return s;
+        if (req_h <= 0 && diff && p.lds_budget < row_lds_bytes(ROW_DIFF_MAX_BAND) &&
+            row_lds_bytes(shape(K, true, 0, ROW_DIFF_MAX_BAND).band_h) > p.lds_budget)
+            return s;
         RowShape rs{};
         for (int form = nms ? 0 : 2; form < 4 && rs.band_h == 0; ++form) {
             s.lists = form < 2;
